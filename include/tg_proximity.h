@@ -14,12 +14,11 @@
  * R_j + radius_rho (2u - 1), u = (2 (x >> 9) + 1) 2^-24 with x the first word of Philox4x32-10,
  * key = seed, counter (env, taxel, step, 9); a per-probe gain (optional) scales the six channels.
  *
- * The library keeps each cloud in a uniform cell grid in the object frame (cell edge = half the
- * largest sensing radius plus radius_rho), points sorted by cell, so a query visits, in each row of
- * cells its sphere reaches, the cells under the sphere's chord as one contiguous run of points;
- * the sums above are formed from two moments
- * accumulated over the visited points, sum P_ij and sum P_ij (p_i - q_j), which give every term of
- * f and tau (the velocity of a point is affine in its position).
+ * The library sorts each cloud into compact chunks of 8 points with bounding spheres in the object
+ * frame; a query evaluates every point of the chunks its sphere may reach (a point outside the
+ * sphere adds exactly 0).  The sums above are formed from two moments accumulated over those points,
+ * sum P_ij and sum P_ij (p_i - q_j), which give every term of f and tau (the velocity of a point
+ * is affine in its position).
  *
  * Conventions are those of tg_readout.h: create deep-copies the host arrays; device buffers are
  * caller-owned and must stay valid until the queued work finishes; calls return a tg_status,
@@ -36,7 +35,7 @@
 extern "C" {
 #endif
 
-typedef struct tg_prox tg_prox; /* opaque: cell grids and sorted clouds on the device */
+typedef struct tg_prox tg_prox; /* opaque: sorted clouds and their bounding spheres on the device */
 
 typedef struct {
   int32_t num_points;   /* >= 0 */

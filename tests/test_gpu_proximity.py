@@ -174,3 +174,41 @@ def test_rejects_bad_configurations(torch_cuda):
     bad[1][3, 0] = np.nan
     with pytest.raises(B.TgError):
         B.Proximity(sc, bad)
+
+
+@pytest.mark.parametrize("counts, points, radius, scale, quat", [
+    ([1, 3, 4, 5, 8, 9, 12, 16, 17, 33], [1, 3, 7, 8, 9, 63, 65, 511], 0.01, 1.0, 1.0),    # tile and chunk remainders
+    ([20] * 5, [513, 4095, 4096, 4097, 1, 0, 17, 8193], 0.01, 1.0, 1.0),   # several envs a workgroup, spheres over 64 groups
+    ([130, 127, 70, 1], [2000] * 8, 0.004, 1.0, 1.0),      # more than one span; tiles smaller than 16 probes
+    ([16, 12, 8], [3000] * 8, 0.01, 256.0, 1.0),           # radii above one: lengths kept in other units
+    ([16, 12, 8], [3000] * 8, 0.01, 1.0, 1.1),             # quaternions are used as given
+    ([16, 20], [9000] * 8, 0.0008, 1.0, 1.0),              # a radius far below the pitch: one probe a tile
+])
+def test_tile_edges(torch_cuda, counts, points, radius, scale, quat):
+    """Sizes at the edges of the tiles (4, 8, 16 probes), chunks (8 points), groups (64) and the
+    spheres over them (4096).  Lengths scale: S0 by `scale`, torques by its square (no velocities
+    there), and the rounding bound of `check` with them."""
+    E, S = 19, 2
+    sc = synth.make_scene("c2", num_envs=E, num_steps=S)
+    sc.layout = synth.make_layout(counts)
+    inp = synth.make_inputs(sc)
+    inp.obj_state = synth.random_object_state(sc, S)
+    inp.link_state[:, 3:7] *= quat
+    clouds = [c[:n] for c, n in zip(synth.surface_clouds(sc.grids, 9000, seed=8), points)]
+    k_s = 10.0 if scale == 1.0 else 0.0
+    f32 = np.float32
+    for a in (inp.link_state, inp.obj_state):
+        a[:, 0:3] *= f32(scale)
+    sc.layout.pos = sc.layout.pos * f32(scale)
+    clouds = [c * f32(scale) for c in clouds]
+    r = float(f32(radius * scale))
+    g_ft, g_m = run_gpu(sc, clouds, inp, radius=r, k_s=k_s)
+    r_ft, r_m, cnt = run_oracle(sc, clouds, inp, radius=r, k_s=k_s)
+    unit = np.array([scale] * 3 + [scale * scale] * 3)[None, :, None, None]
+    vs = velocity_scale(inp, sc)
+    for n in sorted(set(points)):       # the bound's density is the env's object's
+        envs = np.nonzero(np.isin(inp.obj_id[0], [o for o, m in enumerate(points) if m == n]))[0]
+        if envs.size:
+            check((g_ft / unit)[:, :, envs], g_m[:, envs] / scale, ((r_ft / unit)[:, :, envs], r_m[:, envs] / scale, cnt[:, envs]),
+                  vs[:, envs], radius=radius, k_s=k_s, n_pts=max(n, 1))
+    assert radius < 1e-3 or (r_m > 0).any()
