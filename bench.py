@@ -347,7 +347,7 @@ def bench_c2_step(reps: int = 3) -> dict:
     d = B.to_device(inp)
     ro.alloc_outputs(S)
     stream = torch.cuda.current_stream()
-    for s_ in range(S):          # warm-up (graph recorded, then updated per call)
+    for s_ in range(S):          # warm-up
         ro.step(d, s_)
     torch.cuda.synchronize()
     per_step, walls = [], []
@@ -656,7 +656,8 @@ def main():
     ap.add_argument("--no-autotune", action="store_true")
     ap.add_argument("--readouts-per-block", type=int, default=0,
                     help="fix the work plan instead of autotuning (the profiles pin the autotuner's choice)")
-    ap.add_argument("--no-graph", action="store_true")
+    ap.add_argument("--graph", action="store_true", help="replay each rollout from a recorded HIP graph")
+    ap.add_argument("--no-graph", action="store_true", help="plain launches (the default)")
     ap.add_argument("--workload", default="readout", choices=["readout", "c4", "proximity", "audio", "elastomer", "raycast"])
     ap.add_argument("--train-steps", type=int, default=5000)
     ap.add_argument("--nsdf-samples", type=int, default=1 << 17)
@@ -715,8 +716,9 @@ def main():
     if sc.noise.enabled:
         mask |= B.TG_OUT_NOISY
     ro = B.Readout(sc, mask)
-    if args.no_graph:
-        ro.set_graph(False)
+    args.graph = args.graph and not args.no_graph
+    if args.graph:
+        ro.set_graph(True)
     dinp = B.to_device(inp)
     ro.alloc_outputs(S)
     torch.cuda.synchronize()
@@ -768,7 +770,7 @@ def main():
                                   + f" on {len(sc.thermal.field_links)} links"),
                    "envs": E, "taxels": T, "links": L, "steps_per_rollout": S,
                    "readouts_per_block_target": eb, "threads_per_block": threads,
-                   "autotuned": tuned is not None, "graph": not args.no_graph},
+                   "autotuned": tuned is not None, "graph": args.graph},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": measured_traffic(wkey),
                      "kernel": "tg_link_kernel", "algorithmic_bytes_per_launch": nbytes,

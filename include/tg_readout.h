@@ -239,10 +239,11 @@ tg_status tg_readout_poll_errors(tg_readout* h, uint32_t* device_error_flags);
 /* Kernel launch shape the handle uses (for profiling tools): envs per block and threads. */
 tg_status tg_readout_launch_shape(const tg_readout* h, int32_t* envs_per_block, int32_t* threads);
 
-/* Graph mode (default on): rollout records its kernel launches once into a HIP graph on a
- * private stream and replays the graph on `hip_stream`, updating only the launch arguments on
- * later calls.  When `hip_stream` is itself being captured the plain launches are issued
- * instead, so a caller can capture rollout into its own graph. */
+/* Graph mode (default off: rollout issues its launches directly, which costs less host time than
+ * recording them).  On: rollout records its kernel launches into a HIP graph on a private stream
+ * and replays the graph on `hip_stream`, updating only the launch arguments on later calls.  When
+ * `hip_stream` is itself being captured the plain launches are issued in either mode, so a caller
+ * can capture rollout into its own graph.  The results are the same. */
 tg_status tg_readout_set_graph(tg_readout* h, int32_t enable);
 
 /* Autotuner for the readout kernel's work plan: readouts per workgroup 128, 192, 256, 320, 384,

@@ -124,8 +124,8 @@ struct tg_readout {
   int32_t* d_order = nullptr;
   uint16_t* d_silu = nullptr;
   size_t neural_lds = 0;
-  // launch graph of the rollout (recorded on a private stream, replayed on the caller's)
-  int graph_on = 1;
+  // optional launch graph of the rollout (recorded on a private stream, replayed on the caller's)
+  int graph_on = 0;
   hipStream_t cap = nullptr;
   hipGraphExec_t gexec = nullptr;
   // thermal fields
@@ -720,11 +720,6 @@ tg_status tg_readout_create(const tg_readout_config* cfg, tg_readout** out) {
     }
     h->state_bytes += h->field_bytes + h->tmeas_bytes;
   }
-  e = hipStreamCreateWithFlags(&h->cap, hipStreamNonBlocking);
-  if (e != hipSuccess) {
-    tg_readout_destroy(h);
-    return fail(nullptr, TG_ERR_HIP, std::string("stream: ") + hipGetErrorString(e));
-  }
   tg_status st = tg_readout_reset(h, nullptr, 0, nullptr);
   if (st == TG_OK) {
     e = hipDeviceSynchronize();
@@ -799,6 +794,9 @@ tg_status tg_readout_rollout(tg_readout* h, const tg_step_inputs* in, const tg_s
   if (out->link_sums_noisy && !aligned(out->link_sums_noisy, 16))
     return fail(h, TG_ERR_INVALID_ARGUMENT, "link_sums_noisy misaligned");
 
+  // Plain launches by default: a rollout is one to three launches (two per step on the neural
+  // backend), 16 us of host time for a whole step call on 64 envs and 37 us for four neural steps,
+  // against 45 and 55 us when every call records and updates a graph.  The launches are the same.
   // Graph mode: record this call's launches on the private stream, then update the cached
   // executable graph (same kernels and shapes: only the arguments change) and replay it on the
   // caller's stream.  A caller that is itself capturing gets the plain launches.
@@ -928,6 +926,14 @@ tg_status tg_readout_step(tg_readout* h, const tg_step_inputs* in, const tg_step
 
 tg_status tg_readout_set_graph(tg_readout* h, int32_t enable) {
   if (!h) return TG_ERR_INVALID_ARGUMENT;
+  if (enable && !h->cap) {
+    h->err.clear();
+    const hipError_t e = hipStreamCreateWithFlags(&h->cap, hipStreamNonBlocking);
+    if (e != hipSuccess) {
+      h->cap = nullptr;
+      return fail(h, TG_ERR_HIP, std::string("stream: ") + hipGetErrorString(e));
+    }
+  }
   h->graph_on = enable != 0;
   return TG_OK;
 }
