@@ -118,15 +118,25 @@ __global__ void nsdf_targets_kernel(const BoxDesc* __restrict__ boxes, const flo
 // ------------------------------------------------------------------------------------------------
 // A round takes 64 records, one tile of 16 per wave.  Each wave runs its tile forward and back
 // through the network (input gradients on MFMA with the transposed fragments) and stages, for
-// every layer, dz (BF16) and the layer's input activations (BF16) in LDS as [feature][sample].
+// every layer, dz (BF16) and the layer's input activations (BF16) in LDS as [sample][feature] (four
+// features a store; the owners read them transposed with ds_read_b64_tr_b16).
 // After a barrier, the owner of layer l contracts dz_l with the inputs of layer l over the 64
 // samples (16x16x32 MFMA, K = samples of two tiles), so the weight gradient of each layer lives in
 // one wave's accumulators for the whole step.  Bias gradients come from the same staged dz; the
 // output layer's gradient is reduced through a small LDS buffer.
+//
+// Bound: latency of one wave per SIMD (the image and the staging area fill a CU's LDS, the
+// gradients a wave's registers), so what counts is instructions and waits on a wave's own chain.
+// 256 objects x 16384 records a step with the gradient term: 5.65 ms per step when the compiler
+// kept every value it could across the round (512 registers and 70 scratch accesses a round);
+// 3.82 with the lane number and the pre-activations made opaque where a round and its second half
+// begin (no scratch); 3.58 with the staging transposed by the read instead of by 2-byte stores.
+// Eight waves of half the registers, two layers staged at a time, measured the same as four: the
+// registers spilled again.
 namespace {
 
-constexpr int SROW = 20;                    // staging row: 16 samples + pad (u16), 40 bytes
-constexpr int STAGE_U16 = 64 * SROW;        // one [64 feature][16 sample] buffer
+constexpr int SROW = 68;                    // staging row: a sample's 64 features + pad (u16), 136 bytes
+constexpr int STAGE_U16 = 16 * SROW;        // one [16 sample][64 feature] buffer
 constexpr int STAGE_BYTES = 4 * 4 * 2 * STAGE_U16 * 2;   // [wave][layer][dz | act]
 constexpr int RED_FLOATS = 4 * 66 + 4;      // per wave: dw5[64], db5, loss; then the summed loss
 static_assert(B5_OFF == W5_OFF + 64, "db5 follows dw5 in the parameter vector");
@@ -139,29 +149,35 @@ __device__ __forceinline__ uint16_t* stage_buf(uint8_t* smem, int wave, int l, i
   return (uint16_t*)(smem + IMG_BYTES) + ((wave * 4 + l) * 2 + which) * STAGE_U16;
 }
 
-// Stage 16 values held in chain layout (B fragments b[2], lane group g, sample s) as rows of a
-// [feature][sample] buffer.  pe = true: the encoding's own feature order (48 rows).
+// Stage 16 values held in chain layout (B fragments b[2], lane group g, sample s) in sample s's row
+// of a [sample][feature] buffer, four features a store.  pe = true: the encoding's own feature
+// order (48 features).
 __device__ __forceinline__ void stage_frags(uint16_t* buf, const u32x4 b[2], int g, int s, bool pe) {
 #pragma unroll
-  for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-    for (int it = 0; it < 8; ++it) {
-      const uint32_t w = b[kt][it >> 1];
-      const uint16_t v = (uint16_t)((it & 1) ? (w >> 16) : (w & 0xffffu));
-      int row;
-      if (pe) {
-        if (it >= 6) continue;
-        row = 6 * (4 * kt + g) + it;
-      } else {
-        row = 32 * kt + chain_k(g, it);
-      }
-      buf[row * SROW + s] = v;
+  for (int kt = 0; kt < 2; ++kt) {
+    if (pe) {
+      uint32_t* row = (uint32_t*)(buf + s * SROW + 6 * (4 * kt + g));
+      row[0] = b[kt][0];
+      row[1] = b[kt][1];
+      row[2] = b[kt][2];
+    } else {
+      uint16_t* row = buf + s * SROW + 32 * kt + 4 * g;
+      *(u32x2*)row = u32x2{b[kt][0], b[kt][1]};
+      *(u32x2*)(row + 16) = u32x2{b[kt][2], b[kt][3]};
     }
+  }
+}
+// Samples 4 g .. 4 g + 3 of feature f0 + s: the transposing LDS read.  Of the 16 lanes of a group,
+// lane i loads features f0 + 4 (i % 4) .. + 3 of sample 4 g + i / 4 and receives feature f0 + i of the
+// four samples.
+__device__ __forceinline__ u32x2 stage_read(const uint16_t* buf, int f0, int g, int s) {
+  typedef short short4l __attribute__((ext_vector_type(4)));
+  const uint16_t* p = buf + (4 * g + (s >> 2)) * SROW + f0 + 4 * (s & 3);
+  return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4l*)p));
 }
 // Eight samples of one feature row: four from each of two tiles (K order of a 16x16x32 MFMA).
-__device__ __forceinline__ u32x4 stage_pair(const uint16_t* b0, const uint16_t* b1, int row, int g) {
-  const u32x2 x = *(const u32x2*)(b0 + row * SROW + 4 * g);
-  const u32x2 y = *(const u32x2*)(b1 + row * SROW + 4 * g);
+__device__ __forceinline__ u32x4 stage_pair(const uint16_t* b0, const uint16_t* b1, int f0, int g, int s) {
+  const u32x2 x = stage_read(b0, f0, g, s), y = stage_read(b1, f0, g, s);
   return u32x4{x[0], x[1], y[0], y[1]};
 }
 
@@ -448,12 +464,12 @@ __device__ __forceinline__ void owner_wgrad(uint8_t* smem, int L, int lane, f32x
     u32x4 A[4], B[4];
 #pragma unroll
     for (int m = 0; m < 4; ++m) {
-      A[m] = stage_pair(d0, d1, 16 * m + s, g);
+      A[m] = stage_pair(d0, d1, 16 * m, g, s);
       if (bias) dbp[m] += bf_sum8(A[m]);
     }
 #pragma unroll
     for (int n = 0; n < 4; ++n)
-      if (n < nin) B[n] = stage_pair(a0, a1, 16 * n + s, g);
+      if (n < nin) B[n] = stage_pair(a0, a1, 16 * n, g, s);
 #pragma unroll
     for (int m = 0; m < 4; ++m)
 #pragma unroll
@@ -492,7 +508,8 @@ struct FitArgs {
 template <int TRAIN, int GS>
 __global__ __launch_bounds__(NT, 1) void nsdf_fit_kernel(const FitArgs a) {
   extern __shared__ __align__(16) uint8_t smem[];
-  const int o = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4, s = lane & 15;
+  const int o = blockIdx.x, tid = threadIdx.x, lane = tid & 63, g = lane >> 4, s = lane & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int L = wave;                                  // layer owned by this wave
   const int nin = L == 0 ? F : H;
   float* red = (float*)(smem + IMG_BYTES + STAGE_BYTES);
@@ -522,7 +539,12 @@ __global__ __launch_bounds__(NT, 1) void nsdf_fit_kernel(const FitArgs a) {
       }
     }
     for (int rd = 0; rd < rounds; ++rd) {
-      const int64_t j = (int64_t)rd * 64 + wave * 16 + s;
+      // The lane's number is made opaque here, so what the round derives from it (the encoding's
+      // frequencies, feature rows, LDS addresses) is formed again where it is used instead of being
+      // kept in registers across the loop.
+      int lane_ = lane, wave_ = wave;
+      asm volatile("" : "+v"(lane_), "+s"(wave_));
+      const int64_t j = (int64_t)rd * 64 + wave_ * 16 + (lane_ & 15);
       bool valid;
       int64_t idx;
       if (TRAIN) {
@@ -544,18 +566,24 @@ __global__ __launch_bounds__(NT, 1) void nsdf_fit_kernel(const FitArgs a) {
         uint32_t z[4][8], zd[4][8];
         u32x4 pe[2];
         float go;
-        gs_first(im, smem, wave, lane, rec, grec, valid, inv_n, a.pair_lambda, a.grad_lambda, dw5, db5, lossp, tab,
+        gs_first(im, smem, wave_, lane_, rec, grec, valid, inv_n, a.pair_lambda, a.grad_lambda, dw5, db5, lossp, tab,
                  z, pe, zd, go);
         __syncthreads();
-        owner_wgrad(smem, L, lane, acc, dbp, false);   // zdbar against adot
+        owner_wgrad(smem, wave_, lane_, acc, dbp, false);   // zdbar against adot
         __syncthreads();
-        gs_second(im, smem, wave, lane, z, pe, zd, go, tab);
+        // opaque as well: the 64 logistic values per lane are formed again rather than kept
+        asm volatile("" : "+v"(lane_));
+#pragma unroll
+        for (int l = 0; l < 4; ++l)
+#pragma unroll
+          for (int w = 0; w < 8; ++w) asm volatile("" : "+v"(z[l][w]));
+        gs_second(im, smem, wave_, lane_, z, pe, zd, go, tab);
         __syncthreads();
-        owner_wgrad(smem, L, lane, acc, dbp, true);    // zbar against a
+        owner_wgrad(smem, wave_, lane_, acc, dbp, true);    // zbar against a
       } else {
-        tile_backprop(im, smem, wave, lane, rec, valid, inv_n, a.pair_lambda, dw5, db5, lossp, tab);
+        tile_backprop(im, smem, wave_, lane_, rec, valid, inv_n, a.pair_lambda, dw5, db5, lossp, tab);
         __syncthreads();
-        owner_wgrad(smem, L, lane, acc, dbp, true);
+        owner_wgrad(smem, wave_, lane_, acc, dbp, true);
       }
       __syncthreads();
     }
