@@ -176,14 +176,27 @@ __device__ __forceinline__ void pe_frags(float x0, float x1, float x2, int g, u3
   }
 }
 
-// One hidden layer: acc[m] = b + W * in (FP32 accumulation).
-__device__ __forceinline__ void layer_fwd(const Img& im, int l, int lane, const u32x4 bin[2], f32x4 acc[4]) {
+// A hidden layer's forward fragments and biases, on their way from LDS to registers.
+struct LayerFrags {
+  u32x4 w[8];
+  f32x4 b[4];
+};
+__device__ __forceinline__ void load_layer(const Img& im, int l, int lane, LayerFrags& f) {
   const int g = lane >> 4;
 #pragma unroll
   for (int m = 0; m < 4; ++m) {
-    acc[m] = *(const f32x4*)(im.tail + 64 * l + 16 * m + 4 * g);
+    f.b[m] = *(const f32x4*)(im.tail + 64 * l + 16 * m + 4 * g);
 #pragma unroll
-    for (int kt = 0; kt < 2; ++kt) acc[m] = mfma32(frag(im.fwd, (l * 4 + m) * 2 + kt, lane), bin[kt], acc[m]);
+    for (int kt = 0; kt < 2; ++kt) f.w[2 * m + kt] = frag(im.fwd, (l * 4 + m) * 2 + kt, lane);
+  }
+}
+// One hidden layer: acc[m] = b + W * in (FP32 accumulation).
+__device__ __forceinline__ void layer_fwd(const LayerFrags& f, const u32x4 bin[2], f32x4 acc[4]) {
+#pragma unroll
+  for (int m = 0; m < 4; ++m) {
+    acc[m] = f.b[m];
+#pragma unroll
+    for (int kt = 0; kt < 2; ++kt) acc[m] = mfma32(f.w[2 * m + kt], bin[kt], acc[m]);
   }
 }
 
@@ -289,10 +302,15 @@ __device__ __forceinline__ float forward_tile(const Img& im, int lane, float x0,
   pe_frags(x0, x1, x2, g, pe);
   u32x4 b[2] = {pe[0], pe[1]};
   f32x4 acc[4];
+  LayerFrags f;
+  load_layer(im, 0, lane, f);
 #pragma unroll
   for (int l = 0; l < 4; ++l) {
-    __builtin_amdgcn_sched_barrier(0);   // keep each layer's fragment loads next to its MFMAs
-    layer_fwd(im, l, lane, b, acc);
+    __builtin_amdgcn_sched_barrier(0);
+    layer_fwd(f, b, acc);
+    // the next layer's fragments arrive behind this layer's activations (their table lookups end in
+    // a branch, which the loads would not be moved across)
+    if (l < 3) load_layer(im, l + 1, lane, f);
     u32x4 nb[2];
     if (l < 3) {
       activate_tab(acc, z[l], nb, tab);   // layers 1-3 feed a BF16 GEMM: table SiLU
