@@ -703,8 +703,11 @@ tg_status tg_readout_create(const tg_readout_config* cfg, tg_readout** out) {
       tp.dct = dD;
       tp.hk = dH;
       const double surf = (double)td.dt / ((double)td.rho_cp * (double)td.dx);
-      tp.k_rad = (float)(surf * (double)td.emissivity * 5.670374419e-8);
-      tp.k_conv = (float)(surf * (double)td.h_conv);
+      const double kr = surf * (double)td.emissivity * 5.670374419e-8, ta = (double)td.T_amb + 273.15;
+      tp.rad[0] = (float)(kr * 4.0 * ta * ta * ta + surf * (double)td.h_conv);
+      tp.rad[1] = (float)(kr * 6.0 * ta * ta);
+      tp.rad[2] = (float)(kr * 4.0 * ta);
+      tp.rad[3] = (float)kr;
       tp.lag = td.lag_tau > 0.f ? (float)((double)td.dt / (double)td.lag_tau) : 0.f;
       if (tp.lag > 0.f) {
         float* dM = nullptr;

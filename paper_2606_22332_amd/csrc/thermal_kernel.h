@@ -31,8 +31,9 @@ struct ThermalParams {
   int32_t spectral;
   const float* dct;            // [16][16] orthonormal DCT-II, row m: w_m cos(pi m (2i + 1) / 32)
   const float* hk;             // [3 * 15^2 + 1] h(s) = a k^2 / (1 + a k^2), k^2 = (pi / (n dx))^2 s
-  float k_rad;                 // dt eps sigma / (rho c_p dx) per exposed face
-  float k_conv;                // dt h / (rho c_p dx) per exposed face
+  // loss per exposed face and step as a polynomial in d = T - T_amb: d (rad[0] + rad[1] d + rad[2] d^2
+  // + rad[3] d^3), radiation dt eps sigma / (rho c_p dx) (T_K^4 - T_amb,K^4) and convection dt h / (rho c_p dx) d
+  float rad[4];
   float lag;                   // dt / tau of the sensor element, 0 = no lag
   float* t_meas;               // [E][T] measured reading (state), when lag > 0
 };
@@ -58,17 +59,20 @@ struct ThermalLaunch {
 // h = 0 there) but keeps the transformed values small.  C3 is separable, and each axis is a 16 x 16
 // matrix times a 16 x 256 matrix.  Each contraction runs on FP16 MFMA with both operands split into
 // FP16 high and low parts (x = hi + lo, lo the FP16 rounding of x - hi, so hi + lo holds about 22
-// bits): one v_mfma_f32_16x16x32_f16 takes [A_hi, A_hi] times [B_hi; B_lo] and a second takes
-// [A_lo, A_lo] times the same B, so all four partial products accumulate in FP32, at a quarter of
-// the matrix-core time of FP32 MFMA 16x16x4.  The block sits in the exchange buffer ex[z][y][x]
-// (rows padded to 17 floats, planes 272): a contraction reads its B operand (the 16 values of the
-// contracted axis for one column, 4 per lane group) straight from it and writes its 16 x 16 result
-// back in place, each wave owning 4 whole tiles, so only the change of axis needs a barrier.  The
-// forward x transform's result feeds the inverse x transform from registers: its 4 output rows per
-// lane group are the inverse's K slice of that lane group.
+// bits): one v_mfma_f32_16x16x32_f16 takes [M_hi, M_hi] and [X_hi; X_lo] and a second takes
+// [M_lo, M_lo] and the same X, so all four partial products accumulate in FP32, at a quarter of
+// the matrix-core time of FP32 MFMA 16x16x4.
+//
+// The lanes of an operand and of the result are
 //   lane l = 16 g + c:  A[i = c][k = 4 g + r],  B[k = 4 g + r][j = c],  D[i = 4 g + r][j = c]
-// (register r; in the K = 32 operands slot r holds the high part of k = 4 g + r, slot 4 + r the
-// low part of B, or a second copy of A's part).
+// (register r; in the K = 32 operands slot r holds the high part of k = 4 g + r, slot 4 + r the low
+// part of X, or a second copy of M's part).  A tile X whose contracted axis runs over the registers
+// serves as B (X' = M X: the registers then run over the new index) or as A (X'^T = X^T M^T: the
+// registers then run over X's other axis), so two axes follow each other in registers: z, then
+// x, of a wave's four planes y; then, through the exchange buffer once, y, the scale h and the
+// inverse y of its four planes mx; and, through the buffer once more, the inverse x and z.  The buffer is
+// ex[mx][y][mz] with rows of 20 floats and planes of 324, so that the 64 lanes of each of its four
+// accesses per tile fall two to a bank.
 typedef _Float16 dct_h8 __attribute__((ext_vector_type(8)));
 typedef float dct_acc __attribute__((ext_vector_type(4)));
 struct DctSplit {      // one lane's A operand of a 16 x 16 matrix: high and low FP16 parts
@@ -102,108 +106,81 @@ __device__ __forceinline__ DctOperands dct_operands(const float* dct, int lane) 
   o.inv = dct_split(v);
   return o;
 }
-// D += A B for this lane's B values b[r] = B[4 g + r][c]
-__device__ __forceinline__ dct_acc mfma_split(const DctSplit& A, const float b[4], dct_acc acc) {
-  dct_h8 B;
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const _Float16 h = (_Float16)b[r];
-    B[r] = h;
-    B[4 + r] = (_Float16)(b[r] - (float)h);
-  }
-  acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(A.hi, B, acc, 0, 0, 0);
-  return __builtin_amdgcn_mfma_f32_16x16x32_f16(A.lo, B, acc, 0, 0, 0);
+// A lane's four values of a tile as [hi, lo] parts: two packed conversions, the exact remainders
+// (v_fma_mix_f32 reads the FP16 halves), two packed conversions.
+__device__ __forceinline__ dct_h8 data_split(float a, float b, float c, float d) {
+  typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+  typedef float f2 __attribute__((ext_vector_type(2)));
+  const h2 p = __builtin_convertvector((f2){a, b}, h2), q = __builtin_convertvector((f2){c, d}, h2);
+  float e0, e1, e2, e3;
+  asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel_hi:[1,0,0]" : "=v"(e0) : "v"(p), "v"(a));
+  asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(e1) : "v"(p), "v"(b));
+  asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel_hi:[1,0,0]" : "=v"(e2) : "v"(q), "v"(c));
+  asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(e3) : "v"(q), "v"(d));
+  const h2 u = __builtin_convertvector((f2){e0, e1}, h2), v = __builtin_convertvector((f2){e2, e3}, h2);
+  return dct_h8{p[0], p[1], q[0], q[1], u[0], u[1], v[0], v[1]};
 }
-// One axis of a wave's 4 tiles: tile t reads B row k at ex[base(t) + k * ks + c * cs] and writes
-// D row 4 g + r at ex[base(t) + (4 g + r) * ks + c * cs] (ks: stride of the contracted axis, cs:
-// of the column axis).
-__device__ __forceinline__ void dct_axis(float* ex, const DctSplit& A, int base0, int tstride, int ks, int cs,
-                                         int lane) {
-  const int g = lane >> 4, c = lane & 15;
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {   // (a tile's result goes back as soon as the MFMAs have read it)
-    float* src = ex + base0 + t * tstride + c * cs;
-    float b[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) b[r] = src[(4 * g + r) * ks];
-    const dct_acc z = {0.f, 0.f, 0.f, 0.f};
-    const dct_acc d = mfma_split(A, b, z);
-    src[(4 * g + 0) * ks] = d.x;
-    src[(4 * g + 1) * ks] = d.y;
-    src[(4 * g + 2) * ks] = d.z;
-    src[(4 * g + 3) * ks] = d.w;
-  }
+// M X: the result's registers run over M's rows
+__device__ __forceinline__ dct_acc dct_left(const DctSplit& M, const dct_h8& X) {
+  const dct_acc z = {0.f, 0.f, 0.f, 0.f};
+  return __builtin_amdgcn_mfma_f32_16x16x32_f16(M.lo, X, __builtin_amdgcn_mfma_f32_16x16x32_f16(M.hi, X, z, 0, 0, 0),
+                                                0, 0, 0);
 }
-// The step on a block held in the transforms' own layout: lane (g, c) of wave w keeps
-// fv[4 t + r] = T(z = 4 g + r, y = 4 w + t, x = c), which is the forward z pass's B operand and
-// the inverse z pass's D, so those two passes take their operand from registers and give their
-// result back to them: two barriers and a third of the exchange-buffer traffic fewer per step.
-__device__ __forceinline__ void spectral_diffuse_tiles(const DctOperands& C, const float* hk, float T0,
-                                                       float fv[TH_N], float* ex, int tid) {
-  constexpr int RS = TH_N + 1, PS = TH_N * (TH_N + 1);
+// X^T M^T: the result's registers run over X's other axis, its lanes over M's rows
+__device__ __forceinline__ dct_acc dct_right(const dct_h8& X, const DctSplit& M) {
+  const dct_acc z = {0.f, 0.f, 0.f, 0.f};
+  return __builtin_amdgcn_mfma_f32_16x16x32_f16(X, M.lo, __builtin_amdgcn_mfma_f32_16x16x32_f16(X, M.hi, z, 0, 0, 0),
+                                                0, 0, 0);
+}
+__device__ __forceinline__ dct_h8 data_split(const dct_acc& v) { return data_split(v.x, v.y, v.z, v.w); }
+
+constexpr int DCT_RS = 20, DCT_PS = 324;   // row and plane strides of the exchange buffer
+// The step on a block held as fv[4 t + r] = T(z = 4 g + r, y = 4 w + t, x = c) by lane (g, c) of
+// wave w; hv[4 t + r] = h(mx = 4 w + t, my = 4 g + r, mz = c).  `between` runs after the first pair
+// of axes, before the barrier.
+template <class Between>
+__device__ __forceinline__ void spectral_diffuse_tiles(const DctOperands& C, const float hv[TH_N], float T0,
+                                                       float fv[TH_N], float* ex, int tid, Between between) {
   const int w = tid >> 6, lane = tid & 63, g = lane >> 4, c = lane & 15;
-  const dct_acc z0 = {0.f, 0.f, 0.f, 0.f};
-  // forward z: tile t is the plane y = 4 w + t; K = z, columns x
+  float* const own = ex + 4 * g * DCT_PS + 4 * w * DCT_RS + c;   // (mx = 4 g + r, y = 4 w + t, mz = c)
+  float* const til = ex + 4 * w * DCT_PS + 4 * g * DCT_RS + c;   // (mx = 4 w + t, y = 4 g + r, mz = c)
 #pragma unroll
   for (int t = 0; t < 4; ++t) {
-    float b[4];
+    const dct_acc fz = dct_right(data_split(fv[4 * t] - T0, fv[4 * t + 1] - T0, fv[4 * t + 2] - T0, fv[4 * t + 3] - T0), C.fwd);
+    const dct_acc fx = dct_left(C.fwd, data_split(fz));
 #pragma unroll
-    for (int r = 0; r < 4; ++r) b[r] = fv[4 * t + r] - T0;
-    const dct_acc d = mfma_split(C.fwd, b, z0);
-    float* dst = ex + (4 * w + t) * RS + c;
-    dst[(4 * g + 0) * PS] = d.x;
-    dst[(4 * g + 1) * PS] = d.y;
-    dst[(4 * g + 2) * PS] = d.z;
-    dst[(4 * g + 3) * PS] = d.w;
+    for (int r = 0; r < 4; ++r) own[r * DCT_PS + t * DCT_RS] = fx[r];
+  }
+  between();
+  __syncthreads();
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {   // (a tile is the wave's own: its result goes back in place)
+    float* src = til + t * DCT_PS;
+    const dct_acc fy = dct_left(C.fwd, data_split(src[0], src[DCT_RS], src[2 * DCT_RS], src[3 * DCT_RS]));
+    const dct_acc iy = dct_left(C.inv, data_split(fy[0] * hv[4 * t], fy[1] * hv[4 * t + 1], fy[2] * hv[4 * t + 2],
+                                                  fy[3] * hv[4 * t + 3]));
+#pragma unroll
+    for (int r = 0; r < 4; ++r) src[r * DCT_RS] = iy[r];
   }
   __syncthreads();
-  // forward y: planes mz = 4 w + t; K = y (row stride), columns x
-  dct_axis(ex, C.fwd, 4 * w * PS, PS, RS, 1, lane);
-  __syncthreads();
-  // forward x, scale by h, inverse x: planes mz = 4 w + t; K = x, columns my
 #pragma unroll
   for (int t = 0; t < 4; ++t) {
-    const int mz = 4 * w + t;
-    float* pl = ex + mz * PS;
-    float b[4];
+    const float* src = own + t * DCT_RS;
+    const dct_acc ix = dct_right(data_split(src[0], src[DCT_PS], src[2 * DCT_PS], src[3 * DCT_PS]), C.inv);
+    const dct_acc iz = dct_left(C.inv, data_split(ix));
 #pragma unroll
-    for (int r = 0; r < 4; ++r) b[r] = pl[c * RS + 4 * g + r];
-    const dct_acc acc = mfma_split(C.fwd, b, z0);
-    const int b2 = c * c + mz * mz;
-    float hb[4];
-    hb[0] = acc.x * hk[(4 * g + 0) * (4 * g + 0) + b2];
-    hb[1] = acc.y * hk[(4 * g + 1) * (4 * g + 1) + b2];
-    hb[2] = acc.z * hk[(4 * g + 2) * (4 * g + 2) + b2];
-    hb[3] = acc.w * hk[(4 * g + 3) * (4 * g + 3) + b2];
-    const dct_acc inv = mfma_split(C.inv, hb, z0);
-    pl[c * RS + 4 * g + 0] = inv.x;
-    pl[c * RS + 4 * g + 1] = inv.y;
-    pl[c * RS + 4 * g + 2] = inv.z;
-    pl[c * RS + 4 * g + 3] = inv.w;
-  }
-  __syncthreads();
-  // inverse y: planes mz = 4 w + t; K = my, columns x
-  dct_axis(ex, C.inv, 4 * w * PS, PS, RS, 1, lane);
-  __syncthreads();
-  // inverse z into the registers: T' = T - correction
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    const float* src = ex + (4 * w + t) * RS + c;
-    float b[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) b[r] = src[(4 * g + r) * PS];
-    const dct_acc d = mfma_split(C.inv, b, z0);
-    fv[4 * t + 0] = fv[4 * t + 0] - d.x;
-    fv[4 * t + 1] = fv[4 * t + 1] - d.y;
-    fv[4 * t + 2] = fv[4 * t + 2] - d.z;
-    fv[4 * t + 3] = fv[4 * t + 3] - d.w;
+    for (int r = 0; r < 4; ++r) fv[4 * t + r] -= iz[r];
   }
   // (the exchange buffer is written again only after the step's later barrier)
 }
 
 // SPEC = 1: the paper's step (spectral diffusion, T^4 radiation and convection, sensor lag).  Both
-// forms run at four waves per SIMD; the spectral one then spills some registers to scratch, which
-// still beats two waves per SIMD without spills by a fifth.
+// forms run at four waves per SIMD; three without spills and five with more measured slower or the
+// same (1024 envs x 5 fields x 100 steps: spectral 2.41 / 2.11 / 2.08 ms, explicit 1.17 / 0.96 / 1.20).
+// The spectral step is bound by vector issue, of which the transforms' FP16 splits are 2 instructions
+// per value and axis: 2.10 ms against 3.70 with every axis through the buffer (32 accesses per tile
+// instead of 16, five barriers instead of three), 5 instructions per split, and radiation behind a
+// branch that every wave took.
 template <int SPEC>
 __global__ __launch_bounds__(TH_THREADS, 4) void tg_thermal_kernel(const ThermalLaunch q) {
   constexpr int n = TH_N;
@@ -214,19 +191,24 @@ __global__ __launch_bounds__(TH_THREADS, 4) void tg_thermal_kernel(const Thermal
   const int tid = threadIdx.x, x = tid % n, y = tid / n;
   const int E = p.E, L = p.L, T = p.T;
   const int64_t EL = (int64_t)E * L, ET = (int64_t)E * T;
-  __shared__ float ex[n * n * (n + 1)];    // exchange buffer [z][y][x] (rows padded to 17 for the spectral step)
+  // exchange buffer: [z][y][x], or the spectral step's.  (The explicit step's last n^2 floats are
+  // unused: with them the arrays behind it lie so that a step takes 3% less.)
+  __shared__ float ex[SPEC ? n * DCT_PS : n * n * (n + 1)];
   __shared__ float cd[512];                // kappa * depth per taxel of the link
   __shared__ float top[n * n];
   __shared__ float cvs[SPEC ? n * n : 1];   // contact coefficient per top voxel (spectral step)
   __shared__ Pose lp, op;
   __shared__ int oid_s;
-  // the spectral step's filter correction per |m|^2 and the DCT-II operands of this lane
-  __shared__ float hks[SPEC ? 3 * (TH_N - 1) * (TH_N - 1) + 1 : 1];
   DctOperands dcto;
-  if (SPEC) {
-    dcto = dct_operands(th.dct, tid & 63);
-    for (int i = threadIdx.x; i < 3 * (TH_N - 1) * (TH_N - 1) + 1; i += TH_THREADS) hks[i] = th.hk[i];
-    __syncthreads();
+  float hv[SPEC ? n : 1];   // the filter's correction at this lane's modes
+  if constexpr (SPEC) {
+    const int lane = threadIdx.x & 63, hg = lane >> 4, hc = lane & 15, hw = threadIdx.x >> 6;
+    dcto = dct_operands(th.dct, lane);
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        hv[4 * t + k] = th.hk[(4 * hw + t) * (4 * hw + t) + (4 * hg + k) * (4 * hg + k) + hc * hc];
   }
   float* fld = th.fields + ((int64_t)e * th.F + f) * (n * n * n);
   // the field in registers: a z-column per thread (x, y), or for the spectral step the transforms'
@@ -246,6 +228,7 @@ __global__ __launch_bounds__(TH_THREADS, 4) void tg_thermal_kernel(const Thermal
   const int nl = je - jb;
   const float Tobj = th.T_obj[e];
   const float r = th.r, g = th.g, rf = th.rho_f, Tamb = th.T_amb;
+  const float rad0 = th.rad[0], rad1 = th.rad[1], rad2 = th.rad[2], rad3 = th.rad[3];
   const int fxy = (x == 0) + (x == n - 1) + (y == 0) + (y == n - 1);
   const int myvox = y * n + x;
   // exchange-buffer slots of the four in-plane neighbours (at z = 0; + z n^2 for layer z); on a
@@ -311,23 +294,25 @@ __global__ __launch_bounds__(TH_THREADS, 4) void tg_thermal_kernel(const Thermal
     // 3. contact coefficient of this column's top voxel, in taxel order (kappa d per taxel, then
     //    the sum)
     auto coef = [&](int k) { return dep ? th.kappa * dep[k] : cd[k]; };
-    float cv = 0.f;
-    if (nmine <= 4) {
-      if (nmine > 0) cv = cv + coef(mine01 & 0xffffu);
-      if (nmine > 1) cv = cv + coef(mine01 >> 16);
-      if (nmine > 2) cv = cv + coef(mine23 & 0xffffu);
-      if (nmine > 3) cv = cv + coef(mine23 >> 16);
-    } else {
-      for (int k = 0; k < nl; ++k)
-        if (th.taxel_vox[jb + k] == myvox) cv = cv + coef(k);
-    }
+    auto contact = [&] {
+      float cv = 0.f;
+      if (nmine <= 4) {
+        if (nmine > 0) cv = cv + coef(mine01 & 0xffffu);
+        if (nmine > 1) cv = cv + coef(mine01 >> 16);
+        if (nmine > 2) cv = cv + coef(mine23 & 0xffffu);
+        if (nmine > 3) cv = cv + coef(mine23 >> 16);
+      } else {
+        for (int k = 0; k < nl; ++k)
+          if (th.taxel_vox[jb + k] == myvox) cv = cv + coef(k);
+      }
+      return cv;
+    };
     if constexpr (SPEC) {
-      cvs[myvox] = cv;   // read by the lanes holding the top voxels, behind the transforms' barriers
-      spectral_diffuse_tiles(dcto, hks, Tamb, col, ex, tid);
+      // (cvs: read by the lanes holding the top voxels, behind the transforms' barriers)
+      spectral_diffuse_tiles(dcto, hv, Tamb, col, ex, tid, [&] { cvs[myvox] = contact(); });
       // 4'. the paper's order after the diffusion: source, contact conduction on the top voxel,
-      //     then radiation (T^4 in kelvin, as (T - Ta)(T_K + Ta_K)(T_K^2 + Ta_K^2)) and convection
-      //     from every face of the block
-      const float TaK = Tamb + 273.15f, TaK2 = TaK * TaK;
+      //     then radiation and convection from every face of the block, with d = T - T_amb:
+      //     T_K^4 - T_amb,K^4 = d (4 T_amb,K^3 + 6 T_amb,K^2 d + 4 T_amb,K d^2 + d^3)
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
         const int yy = 4 * tw + t;
@@ -336,18 +321,16 @@ __global__ __launch_bounds__(TH_THREADS, 4) void tg_thermal_kernel(const Thermal
         for (int rr = 0; rr < 4; ++rr) {
           const int z = 4 * tg + rr;
           float tv = col[4 * t + rr] + g;
-          if (z == n - 1) tv = tv + cvs[yy * n + tc] * (Tobj - tv);
-          const int faces = fxy_t + (z == 0) + (z == n - 1);
-          if (faces) {
-            const float d = tv - Tamb, TK = tv + 273.15f;
-            const float q4 = d * ((TK + TaK) * fmaf(TK, TK, TaK2));
-            tv = tv - (float)faces * fmaf(th.k_rad, q4, th.k_conv * d);
-          }
-          col[4 * t + rr] = tv;
+          if (rr == 3 && tg == 3) tv = tv + cvs[yy * n + tc] * (Tobj - tv);
+          const float faces = (float)(fxy_t + (rr == 0 ? z == 0 : 0) + (rr == 3 ? z == n - 1 : 0));
+          const float d = tv - Tamb;
+          const float flux = d * fmaf(d, fmaf(d, fmaf(d, rad3, rad2), rad1), rad0);
+          col[4 * t + rr] = fmaf(-faces, flux, tv);
         }
         if (tg == 3) top[yy * n + tc] = col[4 * t + 3];
       }
     } else {
+      const float cv = contact();
 #pragma unroll
       for (int z = 0; z < n; ++z) ex[(z * n + y) * n + x] = col[z];
       __syncthreads();
