@@ -29,6 +29,8 @@
 #include "readout_kernel.h"
 #include "xtalk_dense.h"
 
+#include <type_traits>
+
 namespace tg {
 
 __device__ __forceinline__ void load_pose13(const float* base, int64_t stride, int64_t col, float* v) {
@@ -48,13 +50,24 @@ __device__ __forceinline__ Pose pose_from13(const float* v) {
   return P;
 }
 
-// Outputs are written once and never read back by the kernel: non-temporal stores, so that the
-// output stream does not evict the grid bricks the gathers reuse from L2.
-// Non-temporal store through a uniform base (SGPR pair) and a per-lane 32-bit byte offset: the
-// scalar-base form of the vector store, so no per-lane 64-bit address is formed.  (Outputs are
-// never read by the kernel, so the store needs no ordering against its other memory accesses.)
+// Outputs are written once and never read back by the kernel.  Where a link's run of an output plane
+// covers whole cache lines they go out as non-temporal stores, so that the output stream does not
+// evict the grid bricks the gathers reuse from L2; where runs are short, several links' workgroups
+// share each line, and plain stores let L2 put the line together before it is written
+// (LinkInfo::stream, chosen by plan_links).
+// A store goes through a uniform base (SGPR pair) and a per-lane 32-bit byte offset: the scalar-base
+// form of the vector store, so no per-lane 64-bit address is formed.  (Outputs are never read by the
+// kernel, so the store needs no ordering against its other memory accesses.)
+template <int NT>
 __device__ __forceinline__ void store_at(float* base, uint32_t off4, float v) {
-  asm volatile("global_store_dword %0, %1, %2 nt" : : "v"(off4), "v"(v), "s"(base));
+  if constexpr (NT) asm volatile("global_store_dword %0, %1, %2 nt" : : "v"(off4), "v"(v), "s"(base));
+  else asm volatile("global_store_dword %0, %1, %2" : : "v"(off4), "v"(v), "s"(base));
+}
+// Calls f with the link's store policy as a compile-time constant (a uniform branch).
+template <class F>
+__device__ __forceinline__ void with_policy(int nt, F f) {
+  if (nt) f(std::integral_constant<int, 1>{});
+  else f(std::integral_constant<int, 0>{});
 }
 
 // Two FP32 values rounded to BF16 (nearest even), packed low, high (one v_cvt_pk_bf16_f32).
@@ -132,8 +145,10 @@ __device__ __forceinline__ void link_reduce(KP& p, LI& li, const float* P, int s
     const uint32_t col = (uint32_t)l * (uint32_t)p.E + (uint32_t)e;
     const uint32_t el4 = (uint32_t)EL * 4u;
     const uint32_t o = (uint32_t)(ch < 7 ? ch : ch + 1) * el4 + col * 4u;
-    store_at(out, o, ch < 7 ? acc : 1.0e4f * acc);
-    if (ch == 6) store_at(out, o + el4, acc > 2.5f ? 1.f : 0.f);
+    with_policy(li.stream, [&](auto nt) {
+      store_at<decltype(nt)::value>(out, o, ch < 7 ? acc : 1.0e4f * acc);
+      if (ch == 6) store_at<decltype(nt)::value>(out, o + el4, acc > 2.5f ? 1.f : 0.f);
+    });
   }
 }
 
@@ -325,22 +340,25 @@ __global__ void __launch_bounds__(512, 4) tg_link_kernel(const KLaunch qarg) {
     const bool bit = o.depth > p.eta_on;
     const int wbit = (li.off & 63) + k;   // bit position inside this env's window
     if (act) {
-      if (q.depth) store_at(q.depth + (int64_t)s * ET, off4, o.depth);
-      if (q.prox) store_at(q.prox + (int64_t)s * ET, off4, o.prox);
-      if (FULL && q.surfdist) store_at(q.surfdist + (int64_t)s * ET, off4, o.surf);
-      if (q.ft) {
-        float* f = q.ft + (int64_t)s * 6 * ET;
+      with_policy(li.stream, [&](auto nt) {
+        constexpr int NT = decltype(nt)::value;
+        if (q.depth) store_at<NT>(q.depth + (int64_t)s * ET, off4, o.depth);
+        if (q.prox) store_at<NT>(q.prox + (int64_t)s * ET, off4, o.prox);
+        if (FULL && q.surfdist) store_at<NT>(q.surfdist + (int64_t)s * ET, off4, o.surf);
+        if (q.ft) {
+          float* f = q.ft + (int64_t)s * 6 * ET;
 #pragma unroll
-        for (int c = 0; c < 3; ++c) {
-          store_at(f + c * ET, off4, o.f[c]);
-          store_at(f + (c + 3) * ET, off4, o.tau[c]);
+          for (int c = 0; c < 3; ++c) {
+            store_at<NT>(f + c * ET, off4, o.f[c]);
+            store_at<NT>(f + (c + 3) * ET, off4, o.tau[c]);
+          }
         }
-      }
-      if (FULL && q.normal) {
-        float* nm = q.normal + (int64_t)s * 3 * ET;
+        if (FULL && q.normal) {
+          float* nm = q.normal + (int64_t)s * 3 * ET;
 #pragma unroll
-        for (int c = 0; c < 3; ++c) store_at(nm + c * ET, off4, o.mb[c]);
-      }
+          for (int c = 0; c < 3; ++c) store_at<NT>(nm + c * ET, off4, o.mb[c]);
+        }
+      });
       if (bit) atomicOr(&bw[el * li.nwin * 2 + (wbit >> 5)], 1u << (wbit & 31));
     }
     const bool sums = q.link_sums != nullptr;
@@ -512,8 +530,10 @@ __global__ void __launch_bounds__(512, 4) tg_link_kernel(const KLaunch qarg) {
       }
       if (act && q.ft_noisy) {
         float* f = q.ft_noisy + (int64_t)s * 6 * ET;
+        with_policy(li.stream, [&](auto nt) {
 #pragma unroll
-        for (int c = 0; c < 6; ++c) store_at(f + c * ET, off4, fo[c]);
+          for (int c = 0; c < 6; ++c) store_at<decltype(nt)::value>(f + c * ET, off4, fo[c]);
+        });
       }
       float dd = o.depth;
       if (FULL && p.has_radius) {

@@ -17,6 +17,7 @@ struct LinkInfo {
   int32_t kp, kpd;       // padded K stride (bf16 elements) of the B staging, of the result staging
   int32_t afrag_off;     // first A tile of this link in the fragment buffer
   int32_t np;            // lanes per env: n rounded up to a multiple of 8 (aligned 8-lane groups)
+  int32_t stream;        // 1: non-temporal output stores
 };
 
 // LDS carve-up (byte offsets), identical for every block of a launch.

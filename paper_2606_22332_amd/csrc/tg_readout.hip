@@ -180,6 +180,15 @@ KernelFn select_kernel(int noise, int xt, int hy, int obj, int full) {
 
 // Work plan: envs per block for each link (about `target` readouts per block), the
 // (link, first env) items sorted by env, the LDS carve-up sized for the largest link.
+// Links of this many taxels and more write their outputs with non-temporal stores (LinkInfo::stream).
+// A link of 8 to 40 taxels writes runs of 32 to 160 bytes, so most cache lines are written by two to
+// four workgroups; non-temporal stores sent each part to memory by itself (48 M write requests of
+// 30 bytes per 100 steps of 1024 envs on the 200-taxel hand).  Rollout of that, its thermal step
+// included: 3.13 ms all non-temporal, 2.28 all plain; one step of 4096 envs 78 against 61 us.  On the
+// 1024-taxel hand (links of 25 to 128 taxels, 20480 envs x 16 steps) the line lies in between:
+// 15.87 ms all non-temporal, 15.20 / 14.87 / 14.73 / 14.79 / 14.98 with this bound at 33 / 48 / 64 /
+// 90 / 100, 16.1 all plain; plain stores for the shared lines of a run alone 15.07.
+constexpr int STREAM_MIN_TAXELS = 64;
 tg_status plan_links(tg_readout* h, int target) {
   const int L = h->L, E = h->E;
   const int32_t* off = h->cfg.link_taxel_offset;
@@ -195,6 +204,7 @@ tg_status plan_links(tg_readout* h, int target) {
     li.envs = std::max(1, std::min(std::min(E, 36), target / li.np));
     li.nwin = li.n > 0 ? ((li.off + li.n - 1) >> 6) - (li.off >> 6) + 1 : 1;
     li.nt = (6 * li.envs + 15) / 16;
+    li.stream = li.n >= STREAM_MIN_TAXELS;
     const int n16 = ((li.n + 15) / 16) * 16, n32 = ((li.n + 31) / 32) * 32;
     li.kp = n32 + 8;    // B staging column stride (bf16): K tiles of 32, 16-byte aligned columns
     li.kpd = n16 + 4;   // result staging row stride (floats)
