@@ -2,9 +2,9 @@
 //
 // A block owns one link l for `envs` consecutive environments and runs every step of the
 // launch for them: lane r <-> (env el = r / np, taxel k = r % np), np = n_l rounded up to a
-// multiple of 8, about 192..512 readouts per block whatever the link size, so uneven links waste
-// few lanes, and two blocks share a CU so that one block's memory latency hides behind the
-// other's arithmetic.  Because a block only ever sees one link, everything that couples taxels
+// multiple of 8, about 128..512 readouts per block whatever the link size (the plan's target), so
+// uneven links waste few lanes; the waves that a short link does not need end at once and leave their
+// slots to other blocks, whose memory latency and arithmetic overlap.  Because a block only ever sees one link, everything that couples taxels
 // stays inside the block:
 //   - dense crosstalk C_l Z_l runs on MFMA (16x16x32 BF16) with the six channels of all the
 //     block's envs as the N columns; the link's A fragments are staged in LDS for the launch
@@ -17,7 +17,7 @@
 // readout lives in registers for the whole launch and touches HBM only at its ends.
 //
 // Per step (four barriers): the loader lanes build the rotation matrices from the pose scalars
-// that were prefetched one per lane during the previous step; then the readout (probe point,
+// that were prefetched one or two per lane during the previous step; then the readout (probe point,
 // gathers from the bricked grid, depth, contact, force/torque, proximity), its non-temporal
 // stores (unit-stride runs of n_l floats per env), contact bits into LDS windows and the clean
 // group sums; then the clean epilogue (bit words, link sums) and the crosstalk MFMA; then the
@@ -114,30 +114,20 @@ __device__ __forceinline__ void put_group_sums(float* P, int stride, const float
   }
 }
 
-// A lane's roles in the per-step epilogues, fixed for the launch and packed in one register (byte
-// fields): link sums (channel, env) for lane = channel * envs + env, bit words (env, word) for
-// lane = env * nwin + word.  The plan gives every workgroup at least 14 lanes per env, so each
-// epilogue takes a single pass and the integer divisions happen once, before the step loop.
-__device__ __forceinline__ uint32_t lane_roles(int tid, int envs, int nwin) {
-  const int rch = tid / envs, rel = tid - rch * envs;
-  const int bel = tid / nwin, bw = tid - bel * nwin;
-  const bool rok = rch < 10, bok = bel < envs;
-  return (rok ? (uint32_t)rch | ((uint32_t)rel << 8) : 0xffffu) | (bok ? ((uint32_t)bel << 16) | ((uint32_t)bw << 24) : 0xffff0000u);
-}
-
 // Per-link observations of one step (App. B.2: summed force and torque, contact count, agg_bool,
 // agg_force) from the group partials: one lane per (channel, env) item adds the env's groups in
 // order; output [11][L][E], items env-fastest so neighbouring lanes store neighbouring floats.
+// role: the items' (channel, env) in bytes.
 template <class KP, class LI>
 __device__ __forceinline__ void link_reduce(KP& p, LI& li, const float* P, int stride, int e0, int l,
-                                            float* out, uint32_t roles) {
+                                            float* out, const uint16_t* role) {
   const int gpe = li.np >> 3;
   const int64_t EL = (int64_t)p.E * p.L;
-  {
-    const int ch = roles & 0xffu, el = (roles >> 8) & 0xffu;
-    if (ch >= 10) return;
+  for (int i = threadIdx.x; i < 10 * li.envs; i += li.nthr) {
+    const uint32_t r = role[i];
+    const int ch = r & 0xffu, el = r >> 8;
     const int e = e0 + el;
-    if (e >= p.E) return;
+    if (e >= p.E) continue;
     const float* v = P + ch * stride + el * gpe;
     float acc = 0.f;
     for (int g = 0; g < gpe; ++g) acc += v[g];
@@ -157,13 +147,13 @@ __device__ __forceinline__ void link_reduce(KP& p, LI& li, const float* P, int s
 // a bit set; a word shared with a neighbouring link receives this link's nonzero bits by atomic or.
 template <class KP, class LI>
 __device__ __forceinline__ void store_bits(KP& p, LI& li, const unsigned* win, int e0,
-                                           unsigned long long* out_step, uint32_t roles) {
+                                           unsigned long long* out_step, const uint16_t* role) {
   const int nw = li.nwin;
   const int wstart = li.off >> 6;
   const int lo = li.off, hi = li.off + li.n;
-  {
-    const int el = (roles >> 16) & 0xffu, w = roles >> 24;
-    if (el >= li.envs) return;
+  if ((int)threadIdx.x < li.envs * nw) {
+    const uint32_t r = role[threadIdx.x];   // (word, env) in bytes
+    const int el = r >> 8, w = r & 0xffu;
     const int e = e0 + el;
     if (e >= p.E) return;
     const unsigned long long bits =
@@ -215,11 +205,14 @@ __global__ void __launch_bounds__(512, 4) tg_link_kernel(const KLaunch qarg) {
 #define li (*lip)
   const int n = li.n, envs = li.envs;
   const int tid = threadIdx.x;
-  const int nthr = blockDim.x;
+  // The threads this link needs; the waves past them end here (a barrier counts the waves that are
+  // left), so short links do not hold wave slots that the launch's longest link asked for.
+  const int nthr = li.nthr;
+  if (tid >= nthr) return;
   LinkLds Ld;   // field by field: the source lives in the constant address space
   Ld.pose = p.lds.pose; Ld.opose = p.lds.opose; Ld.oid = p.lds.oid; Ld.bits = p.lds.bits; Ld.sums = p.lds.sums;
   Ld.xz = p.lds.xz; Ld.tax = p.lds.tax; Ld.gtab = p.lds.gtab; Ld.raw = p.lds.raw; Ld.bt = p.lds.bt; Ld.dt = p.lds.dt;
-  Ld.afr = p.lds.afr; Ld.total = p.lds.total;
+  Ld.afr = p.lds.afr; Ld.role = p.lds.role; Ld.total = p.lds.total;
   Pose* lpose = (Pose*)(smem + Ld.pose);
   Pose* opose = (Pose*)(smem + Ld.opose);
   int* oids = (int*)(smem + Ld.oid);
@@ -229,6 +222,11 @@ __global__ void __launch_bounds__(512, 4) tg_link_kernel(const KLaunch qarg) {
   float4* TX = (float4*)(smem + Ld.tax);     // [n][2]: (x_j, R_j), (n_j, link)
   GridDesc* GT = (GridDesc*)(smem + Ld.gtab);
   float* RAW = (float*)(smem + Ld.raw);      // [2][14][envs] prefetched step inputs
+  // The step loop's index arithmetic, done once: (channel, env) of each link-sum item, (word, env)
+  // of each bit word, in bytes; and where each of the 14 envs input scalars lies.
+  uint16_t* SUMROLE = (uint16_t*)(smem + Ld.role);
+  uint16_t* BITROLE = SUMROLE + 10 * envs;
+  int* PFOFF = (int*)(smem + Ld.role + ((20 * envs + 2 * envs * li.nwin + 3) & ~3));
   const int winw = envs * li.nwin * 2;       // u32 words of one bit-window set
 
   const int np = li.np;                      // lanes per env (n padded to a multiple of 8)
@@ -243,7 +241,6 @@ __global__ void __launch_bounds__(512, 4) tg_link_kernel(const KLaunch qarg) {
   // byte offset of (e, j) in an [E][T] plane: fits 32 bits (checked at create), so every output
   // store is a uniform per-step base plus this fixed lane offset
   const uint32_t off4 = (uint32_t)kk * 4u;
-  const uint32_t roles = lane_roles(tid, envs, li.nwin);
 
   for (int i = tid; i < n; i += nthr) {
     TX[2 * i] = p.taxA[li.off + i];
@@ -251,22 +248,29 @@ __global__ void __launch_bounds__(512, 4) tg_link_kernel(const KLaunch qarg) {
   }
   if (p.gtab_lds)
     for (int i = tid; i < p.n_obj; i += nthr) GT[i] = p.grids[i];
-  // Step inputs: scalar c (13 link-pose values, then the object id) of env el at step s is
-  // parked at RAW[(s&1)][c][el].  Lane i < 14*envs owns scalar (c = i / envs, el = i % envs)
-  // for every step: one pointer and one per-step stride, fixed for the launch.
-  // Offsets are packed in one int per lane: >= 0 into link_state (per step +13*E*L), < -1 the
-  // object id -(off+2) (per step +E), -1 none.
-  const int nraw = 14 * envs;
-  int pf_off = -1;
-  if (tid < nraw) {
-    const int c = tid / envs, el_ = tid - c * envs;
-    if (e0 + el_ < p.E) pf_off = c < 13 ? (int)(c * EL + (int64_t)(e0 + el_) * p.L + l) : -(e0 + el_) - 2;
+  for (int i = tid; i < 10 * envs; i += nthr) {
+    const int c = i / envs;
+    SUMROLE[i] = (uint16_t)(c | ((i - c * envs) << 8));
   }
-  auto prefetch = [&](int s_) -> float {
-    if (pf_off >= 0) return q.link_state[(int64_t)s_ * 13 * EL + pf_off];
-    return __int_as_float(q.obj_id[(int64_t)s_ * p.E + (-pf_off - 2)]);
+  if (tid < envs * li.nwin) {
+    const int el_ = tid / li.nwin;
+    BITROLE[tid] = (uint16_t)((tid - el_ * li.nwin) | (el_ << 8));
+  }
+  // Step inputs: scalar c (13 link-pose values, then the object id) of env el at step s is
+  // parked at RAW[(s&1)][c][el].  Lane i takes scalars i and i + nthr (c = i / envs, el = i % envs).
+  // PFOFF: >= 0 an offset into link_state (per step +13*E*L), < -1 the object id -(off+2) (per step
+  // +E), -1 none (an env past the last).
+  const int nraw = 14 * envs;
+  for (int i = tid; i < nraw; i += nthr) {
+    const int c = i / envs, el_ = i - c * envs;
+    PFOFF[i] = e0 + el_ >= p.E ? -1 : (c < 13 ? (int)(c * EL + (int64_t)(e0 + el_) * p.L + l) : -(e0 + el_) - 2);
+  }
+  auto prefetch = [&](int s_, int i) -> float {
+    const int off = PFOFF[i];
+    if (off >= 0) return q.link_state[(int64_t)s_ * 13 * EL + off];
+    return off == -1 ? 0.f : __int_as_float(q.obj_id[(int64_t)s_ * p.E + (-off - 2)]);
   };
-  if (pf_off != -1) RAW[tid] = prefetch(0);
+  for (int i = tid; i < nraw; i += nthr) RAW[i] = prefetch(0, i);
   float D[6] = {0, 0, 0, 0, 0, 0}, Y[6] = {0, 0, 0, 0, 0, 0}, XP[6] = {0, 0, 0, 0, 0, 0};
   uint32_t yd2 = 0u, yd3 = 0u;               // carried-over pair of the drift stream
   bool sch = false, dead = false;
@@ -322,10 +326,16 @@ __global__ void __launch_bounds__(512, 4) tg_link_kernel(const KLaunch qarg) {
     for (int i = tid; i < 2 * winw; i += nthr) bw[i] = 0u;
     __syncthreads();   // B1: poses, ids, zeroed bit windows
     TG_REFRESH_PHASE();
-    // prefetch this lane's scalar of the next step's inputs; parked in LDS before the last barrier
+    // prefetch this lane's scalars of the next step's inputs; parked in LDS before the last barrier
     const bool pre = s + 1 < q.n_steps;
-    float rv = 0.f;
-    if (pre && pf_off != -1) rv = prefetch(s + 1);
+    const bool pre0 = pre && tid < nraw, pre1 = pre && tid + nthr < nraw;
+    float rv = 0.f, rv1 = 0.f;
+    if (pre0) rv = prefetch(s + 1, tid);
+    if (pre1) rv1 = prefetch(s + 1, tid + nthr);
+    auto park = [&] {
+      if (pre0) RAW[(par ^ 1) * nraw + tid] = rv;
+      if (pre1) RAW[(par ^ 1) * nraw + tid + nthr] = rv1;
+    };
 
     const float4 ta = act ? TX[2 * k] : make_float4(0.f, 0.f, 0.f, 0.f);
     const float4 tb = act ? TX[2 * k + 1] : make_float4(0.f, 0.f, 0.f, 0.f);
@@ -383,11 +393,11 @@ __global__ void __launch_bounds__(512, 4) tg_link_kernel(const KLaunch qarg) {
         brow[(c + 1) * kp] = (uint16_t)(w >> 16);
       }
     }
-    if (!NOISE && pre && pf_off != -1) RAW[(par ^ 1) * nraw + tid] = rv;   // the other parity is free
+    if (!NOISE) park();   // the other parity is free
     __syncthreads();   // B2: clean bits, sums, crosstalk operands
     TG_REFRESH_PHASE();
-    if (q.bits) store_bits(p, li, bw, e0, q.bits + (int64_t)s * p.E * p.W, roles);
-    if (sums) link_reduce(p, li, S, sstride, e0, l, q.link_sums + (int64_t)s * 11 * EL, roles);
+    if (q.bits) store_bits(p, li, bw, e0, q.bits + (int64_t)s * p.E * p.W, BITROLE);
+    if (sums) link_reduce(p, li, S, sstride, e0, l, q.link_sums + (int64_t)s * 11 * EL, SUMROLE);
 
     if (NOISE) {
       if (XT >= 2) {
@@ -559,11 +569,11 @@ __global__ void __launch_bounds__(512, 4) tg_link_kernel(const KLaunch qarg) {
                              act && nb ? 1.f : 0.f, dd * tn.z, dd * tn.y, dd * tn.x};
         put_group_sums(S, sstride, v);
       }
-      if (pre && pf_off != -1) RAW[(par ^ 1) * nraw + tid] = rv;   // park the next step's inputs
+      park();   // the next step's inputs
       __syncthreads();   // B4: noisy bits and sums
       TG_REFRESH_PHASE();
-      if (q.bits_noisy) store_bits(p, li, bwn, e0, q.bits_noisy + (int64_t)s * p.E * p.W, roles);
-      if (sums_n) link_reduce(p, li, S, sstride, e0, l, q.link_sums_noisy + (int64_t)s * 11 * EL, roles);
+      if (q.bits_noisy) store_bits(p, li, bwn, e0, q.bits_noisy + (int64_t)s * p.E * p.W, BITROLE);
+      if (sums_n) link_reduce(p, li, S, sstride, e0, l, q.link_sums_noisy + (int64_t)s * 11 * EL, SUMROLE);
     }
   }
   TG_REFRESH();

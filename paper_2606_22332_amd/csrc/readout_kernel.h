@@ -18,11 +18,12 @@ struct LinkInfo {
   int32_t afrag_off;     // first A tile of this link in the fragment buffer
   int32_t np;            // lanes per env: n rounded up to a multiple of 8 (aligned 8-lane groups)
   int32_t stream;        // 1: non-temporal output stores
+  int32_t nthr;          // threads of a workgroup that work on this link (whole waves)
 };
 
 // LDS carve-up (byte offsets), identical for every block of a launch.
 struct LinkLds {
-  int32_t pose, opose, oid, bits, sums, xz, tax, gtab, raw, bt, dt, afr, total;
+  int32_t pose, opose, oid, bits, sums, xz, tax, gtab, raw, bt, dt, afr, role, total;
 };
 
 struct KParams {

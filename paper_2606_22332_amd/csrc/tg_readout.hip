@@ -189,6 +189,17 @@ KernelFn select_kernel(int noise, int xt, int hy, int obj, int full) {
 // 15.87 ms all non-temporal, 15.20 / 14.87 / 14.73 / 14.79 / 14.98 with this bound at 33 / 48 / 64 /
 // 90 / 100, 16.1 all plain; plain stores for the shared lines of a run alone 15.07.
 constexpr int STREAM_MIN_TAXELS = 64;
+// Most envs of a workgroup: 8-taxel links then fill 512 lanes.  (36, one prefetched scalar a lane,
+// and idle waves kept: 200-taxel hand, 1021 envs x 33 steps 595 us against 385, one step of 4096
+// envs 62 against 58.)
+constexpr int MAX_ENVS = 64;
+// Readouts per workgroup of a new handle (the autotuner and set_work_plan change it).  Dense crosstalk
+// stages a link's matrix per workgroup, so large ones pay: 1024-taxel hand, 20480 envs x 16 steps
+// 14.5 ms at 512, 15.3 at 256, 17.3 at 128.  Without it a workgroup shares nothing but its barriers:
+// with noise 128 (200-taxel hand, 1024 envs x 100 steps 0.98 ms, 1.04 at 256, 1.02 at 512; one step
+// of 4096 envs 51.6 us, 51.9, 54.6), and 256 for the shorter clean readout, whose workgroups
+// otherwise spend their time starting (2000 envs x 16 steps 188 us, 192 at 128, 199 at 512).
+int default_target(const tg_readout* h) { return h->xt == 2 ? 512 : (h->noise ? 128 : 256); }
 tg_status plan_links(tg_readout* h, int target) {
   const int L = h->L, E = h->E;
   const int32_t* off = h->cfg.link_taxel_offset;
@@ -198,34 +209,30 @@ tg_status plan_links(tg_readout* h, int target) {
     li.off = off[l];
     li.n = off[l + 1] - off[l];
     if (li.n > 512) return TG_ERR_UNSUPPORTED;
-    // envs per block: ~target readouts, at most 36 envs so that the 14 prefetched scalars per env
-    // fit one per lane
+    // envs per block: ~target readouts
     li.np = li.n > 0 ? (li.n + 7) & ~7 : 8;   // lanes per env: whole 8-lane groups
-    li.envs = std::max(1, std::min(std::min(E, 36), target / li.np));
+    li.envs = std::max(1, std::min(std::min(E, MAX_ENVS), target / li.np));
     li.nwin = li.n > 0 ? ((li.off + li.n - 1) >> 6) - (li.off >> 6) + 1 : 1;
     li.nt = (6 * li.envs + 15) / 16;
     li.stream = li.n >= STREAM_MIN_TAXELS;
     const int n16 = ((li.n + 15) / 16) * 16, n32 = ((li.n + 31) / 32) * 32;
     li.kp = n32 + 8;    // B staging column stride (bf16): K tiles of 32, 16-byte aligned columns
     li.kpd = n16 + 4;   // result staging row stride (floats)
-    nthr = std::max(nthr, ((li.envs * li.np + 63) / 64) * 64);
-  }
-  {  // the per-step input prefetch parks 14 scalars per env, one per lane
-    int max_envs = 1;
-    for (int l = 0; l < L; ++l) max_envs = std::max(max_envs, h->links[l].envs);
-    nthr = std::max(nthr, ((14 * max_envs + 63) / 64) * 64);
+    // whole waves for the readouts, for the 14 prefetched scalars per env at two a lane, and for one
+    // bit word a lane
+    li.nthr = ((std::max(std::max(li.envs * li.np, 7 * li.envs), li.envs * li.nwin) + 63) / 64) * 64;
+    nthr = std::max(nthr, li.nthr);
   }
   if (nthr > 512) return TG_ERR_UNSUPPORTED;
-  for (int l = 0; l < L; ++l)   // the per-step epilogues take one pass: one lane per item
-    if (10 * h->links[l].envs > nthr || h->links[l].envs * h->links[l].nwin > nthr) return TG_ERR_UNSUPPORTED;
   h->threads = nthr;
   // LDS layout: max over links of each region
-  int64_t pose = 0, bits = 0, bt = 0, dt = 0, tax = 0;
+  int64_t pose = 0, bits = 0, bt = 0, dt = 0, tax = 0, role = 0;
   for (int l = 0; l < L; ++l) {
     const LinkInfo& li = h->links[l];
     pose = std::max<int64_t>(pose, li.envs);
     bits = std::max<int64_t>(bits, (int64_t)li.envs * li.nwin * 2);
     tax = std::max<int64_t>(tax, (int64_t)li.n * 32);
+    role = std::max<int64_t>(role, ((20 * li.envs + 2 * li.envs * li.nwin + 3) & ~3) + 14 * 4 * li.envs);
     if (h->xt == 2) {
       bt = std::max<int64_t>(bt, (int64_t)li.nt * 16 * li.kp * 2);
       dt = std::max<int64_t>(dt, (int64_t)6 * li.envs * li.kpd * 4);
@@ -243,6 +250,7 @@ tg_status plan_links(tg_readout* h, int target) {
   h->kp.gtab_lds = h->n_obj <= 256;
   d.gtab = (int32_t)o; o = align16i(o + (h->kp.gtab_lds ? (int64_t)h->n_obj * (int64_t)sizeof(GridDesc) : 0));
   d.raw = (int32_t)o; o = align16i(o + 2 * 14 * pose * 4);
+  d.role = (int32_t)o; o = align16i(o + role);
   d.bt = (int32_t)o; o = align16i(o + bt);
   d.dt = (int32_t)o; o = align16i(o + dt);
   // the dense crosstalk A fragments of the largest link, resident in LDS when they fit
@@ -582,7 +590,7 @@ tg_status tg_readout_create(const tg_readout_config* cfg, tg_readout** out) {
     k.xt_afrag = h->xtd.afrag;
   }
   {
-    tg_status st = plan_links(h, 512);
+    tg_status st = plan_links(h, default_target(h));
     if (st != TG_OK) {
       tg_readout_destroy(h);
       return fail(nullptr, st, st == TG_ERR_UNSUPPORTED ? "a link has more than 512 taxels"

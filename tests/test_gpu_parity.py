@@ -452,3 +452,45 @@ def test_zero_step_rollout_is_a_no_op(torch_cuda):
     assert torch.equal(st0, st1)
     ro.out = {}
     ro.close()
+
+
+@pytest.mark.parametrize("counts, E, noise", [
+    ([8] * 5 + [1, 7, 9], 65, "banded"),           # one env past a workgroup of 64; waves that end early
+    ([64, 65, 130, 8], 17, "banded"),              # links on both sides of the store policy's bound
+    ([512, 1, 40], 3, "banded"),                   # the longest link beside the shortest
+    ([16, 24, 33], 37, "dense"),
+    ([8, 20, 63, 64], 130, "off"),
+])
+def test_plans_agree(torch_cuda, counts, E, noise):
+    """The plan, and with it the threads of each link, the input prefetch and the epilogues' items,
+    changes nothing: the default plan equals the oracle, and every other plan equals it bit for
+    bit (a link's sums add the same 8-lane groups in the same order whatever the plan)."""
+    torch = torch_cuda
+    from paper_2606_22332_amd import binding as B
+    S = 3
+    sc = synth.make_scene("c2", num_envs=E, num_steps=S)
+    sc.layout = synth.make_layout(counts)
+    if noise == "off":
+        sc.noise = synth.NoiseParams(seed=sc.noise.seed)
+    elif noise == "dense":
+        sc.noise.xtalk_kind, sc.noise.xtalk_chi, sc.noise.xtalk_sigma = 2, 0.1, 2e-3
+    inp = synth.make_inputs(sc)
+    inp.obj_state = synth.random_object_state(sc, S)
+    d = B.to_device(inp)
+    res = []
+    for plan in (None, 64, 128, 512):
+        ro = B.Readout(sc)
+        ro.alloc_outputs(S)
+        if plan is not None:
+            ro.set_work_plan(plan)
+        ro.rollout(d, S)
+        torch.cuda.synchronize()
+        res.append({k: v.cpu().numpy() for k, v in ro.out.items()})
+        ro.out = {}
+        ro.close()
+    ref = oracle_ref(sc, inp)
+    parity.compare(res[0], ref, sc.layout.num_taxels, noisy=noise != "off", sigma=sc.noise.drift_sigma,
+                   link_offset=sc.layout.link_offset)
+    for other in res[1:]:
+        for k, v in res[0].items():
+            assert np.array_equal(v, other[k]), k
