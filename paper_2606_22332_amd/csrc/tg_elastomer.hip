@@ -1,25 +1,31 @@
 // ElastomerTaxel (App. A.7) behind include/tg_elastomer.h.
 //
-// Work layout.  One wave per (env, sensor link), persistent over the steps of a launch.  The
-// object's tracked points are spread over the lanes (lane + 64 k, k < PPL) and their anchors
-// stay in registers for the whole launch (read once, written once).  Per step:
-//   1. poses (uniform loads), the object-change check;
-//   2. the link's source probes with h_i > 0 go to an LDS list (ballot compaction);
-//   3. the points: create sorts each cloud along a Morton curve and cuts it into chunks of 64
-//      (chunk k = the k-th point of every lane) with a bounding sphere each.  Lane k places chunk
-//      k's centre in the sensor frame; a chunk whose sphere stays farther than eta_exit from the
-//      pad (pad SDF at the centre minus the radius, with a 1 um margin for rounding) can hold no
-//      anchor and no contact, so its anchors are dropped, as the per-point rule would drop them,
-//      and its points are skipped.  The other points get their sensor-frame position, pad SDF and
-//      anchor update in the fixed FP32 sequence; points that are anchored and inside the pad go
-//      to an LDS list, which is consumed into the markers' accumulators whenever it could
-//      overflow (and at the end);
+// Work layout.  One wave per (env, sensor link), persistent over the steps of a launch.  Per step:
+//   1. poses: half the lanes convert the link's, half the object's, a step ahead of their use; the
+//      object-change check;
+//   2. the link's source probes with h_i > 0 go to an LDS list (ballot compaction); the S splits of
+//      the marker lanes (4) take the depths and powers of S steps at once;
+//   3. the points: create sorts each cloud along a Morton curve and cuts it into runs of 8 with a
+//      bounding sphere each.  Lane k places the centres of the runs k and k + 64 in the sensor
+//      frame; a run whose sphere stays farther than eta_exit from the pad (distance to the box
+//      minus the radius, with a margin for rounding) can hold no anchor and no contact, so its
+//      anchors are dropped, as the per-point rule would drop them, and its points are skipped.  The
+//      other runs are taken 8 at a time, a lane a point: sensor-frame position, pad SDF and anchor
+//      update in the fixed FP32 sequence; points that are anchored and inside the pad go to an LDS
+//      list, which is consumed into the markers' accumulators whenever it could overflow (and at
+//      the end).  Which points are anchored is a bit each in LDS; the anchors stay in memory, where
+//      only the points with one read it (a few dozen of a cloud);
 //   4. the markers: lane L serves marker L % nl with split L / nl of the terms (S = 64 / nl
 //      splits), so a 20-marker fingertip keeps 60 lanes busy; the splits' partial sums meet in
 //      LDS in split order, and the marker's lane writes y_j.
-// All LDS regions belong to the one wave, so barriers are cheap.  The work is FP32 ALU (an
-// exponential and about 30 operations per (marker, term)); the bytes are the points (L2),
-// the depths of the link and the displacements out.
+// All LDS regions belong to the one wave, so barriers are cheap.
+// Bound: VALU issue (96% of the SIMDs' cycles), so what counts is instructions; the bytes are the
+// points (L2), the depths of the link and the displacements out.  4096 envs x 5 pads x 32 steps,
+// 1000-point clouds: 2.78 ms with the anchors of 16 chunks of 64 points in registers (1990 vector
+// instructions a step, of which about half moved the anchor arrays from block to block, 2 waves a
+// SIMD), 0.92 ms with the anchors in memory and a loop over the near chunks, 0.88 ms with the poses
+// converted once and ahead, 0.59 ms with runs of 8 (a pad is near 6 chunks but few of their runs)
+// and the powers of S steps at once (507 instructions, 7 waves).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -37,6 +43,8 @@ namespace {
 thread_local std::string g_elast_create_error;
 constexpr int EL_MAX_MARKERS = 64;
 constexpr int EL_MAX_POINTS = 1024;
+constexpr int EL_RUN = 8;           // points per bounding sphere
+constexpr int EL_RUNS = EL_MAX_POINTS / EL_RUN;
 constexpr int EL_LIST = 128;        // contact-list capacity (two waves' worth of points)
 
 struct ElastParams {
@@ -49,9 +57,10 @@ struct ElastParams {
   const float4* pad;             // [Ls][2] (centre, 0), (half, 0)
   const int32_t* cloud_off;      // [n_obj + 1]
   const float4* pts;             // object-frame points (x, y, z, 0), Morton order per object
-  const int32_t* chunk_off;      // [n_obj + 1] first chunk of each object
-  const float4* chunks;          // bounding sphere (centre, radius) of each run of 64 points
-  float4* anchor;                // [E][Ls][max_pts] (e_p, active as 0 / 1)
+  const int32_t* run_off;        // [n_obj + 1] first run of each object
+  const float4* spheres;         // bounding sphere (centre, radius) of each run of EL_RUN points
+  float4* anchor;                // [E][Ls][max_pts] (e_p, 0), read only where active
+  uint32_t* active;              // [E][Ls][EL_RUNS / 4] a byte a run: bit i, its point i has an anchor
   int32_t* last_oid;             // [E][Ls]
 };
 
@@ -79,13 +88,25 @@ __device__ __forceinline__ void tproj(float v0, float v1, float v2, float n0, fl
   o1 = fmaf(-d, n1, v1);
   o2 = fmaf(-d, n2, v2);
 }
+// one lane's value as a uniform one
+__device__ __forceinline__ float uni(float v, int lane) {
+  return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), lane));
+}
+// the number of lanes below this one in a ballot
+__device__ __forceinline__ int rank_of(uint64_t bal) {
+  return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
+}
 }  // namespace
 
-template <int PPL>
-__global__ __launch_bounds__(64) void tg_elast_kernel(const ElastParams p, const ElastLaunch q) {
-  __shared__ float4 src_a[EL_MAX_MARKERS], src_b[EL_MAX_MARKERS];   // (x_i, h_i), (h_i^alpha, ...)
-  __shared__ float4 lst_a[EL_LIST], lst_b[EL_LIST];                 // (z_p, h_p), (z_p - e_p, 0)
-  __shared__ float red[3][64];
+// 7 waves a SIMD (72 registers): before the runs of 8, 0.87 ms against 0.89 with 6 and 1.00 with 8
+// (which spills)
+__global__ __launch_bounds__(64, 7) void tg_elast_kernel(const ElastParams p, const ElastLaunch q) {
+  // the sources, then the contact list, then the splits' sums: one at a time
+  __shared__ float4 buf_a[EL_LIST];   // (x_i, h_i) | (z_p, h_p) | y0, y1
+  __shared__ float4 buf_b[EL_LIST];   // (h_i^alpha, ...) | (z_p - e_p, 0) | y2
+  __shared__ uint32_t act_w[EL_RUNS / 4];   // a byte a run: bit i, its point i has an anchor
+  __shared__ uint8_t runs[EL_RUNS];         // the runs that can touch the pad in this step
+  uint8_t* const act_b = (uint8_t*)act_w;
   const int lane = threadIdx.x;
   const int e = blockIdx.x / p.Ls, li = blockIdx.x - e * p.Ls;
   const int l = p.sensor_links[li];
@@ -101,63 +122,91 @@ __global__ __launch_bounds__(64) void tg_elast_kernel(const ElastParams p, const
     xj = p.tax[j0 + jj];
     nj = p.nrm[j0 + jj];
   }
-  // anchors in registers
   const int64_t sl = (int64_t)e * p.Ls + li;
-  float ax[PPL], ay[PPL], az[PPL];
-  uint32_t act = 0;
-#pragma unroll
-  for (int k = 0; k < PPL; ++k) {
-    const int idx = lane + 64 * k;
-    float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (idx < p.max_pts) a = p.anchor[sl * p.max_pts + idx];
-    ax[k] = a.x; ay[k] = a.y; az[k] = a.z;
-    if (a.w != 0.f) act |= 1u << k;
-  }
+  float4* const anchor = p.anchor + sl * p.max_pts;
+  if (lane < EL_RUNS / 4) act_w[lane] = p.active[sl * (EL_RUNS / 4) + lane];
   int last = p.last_oid[sl];
+  // poses: lanes 0..31 read and convert the link's, lanes 32..63 the object's, a step ahead
+  const bool obj = lane >= 32;
+  const bool posed = !obj || q.obj_state;
+  const float* pose = obj ? q.obj_state + e : q.link_state + (int64_t)e * p.L + l;
+  const int64_t pstride = obj ? (int64_t)p.E : EL;
+  float pz[7] = {0.f, 0.f, 0.f, 1.f, 0.f, 0.f, 0.f};
+  int oidn = -1;
+  auto fetch = [&](int s) {
+    if (posed) {
+#pragma unroll
+      for (int i = 0; i < 7; ++i) pz[i] = pose[((int64_t)s * 13 + i) * pstride];
+    }
+    oidn = q.obj_id[(int64_t)s * p.E + e];
+  };
+  fetch(0);
+  // depths: split g of a marker reads the step s + g, so S steps take their powers at once
+  const float* dep = q.depth + (int64_t)g * ET + (int64_t)e * p.T + j0 + jj;
+  float dn = 0.f, h = 0.f, hpow = 0.f;
+  if (mlane && g < q.n_steps) dn = dep[0];
+  int sg = S;   // the split whose depths this step takes
+  int np = 0;
+  const float4* pts = p.pts;
+  float4 cs[EL_RUNS / 64];   // lane k: the bounding spheres of the runs k, k + 64
+#pragma unroll
+  for (int t = 0; t < EL_RUNS / 64; ++t) cs[t] = make_float4(0.f, 0.f, 0.f, 0.f);
 
   for (int s = 0; s < q.n_steps; ++s) {
-    const int oid = q.obj_id[(int64_t)s * p.E + e];
-    if (oid != last) {
-      act = 0;
+    const int oid = __builtin_amdgcn_readfirstlane(oidn);
+    if (s == 0 || oid != last) {
+      np = 0;
+      if (oid >= 0 && oid < p.n_obj) {
+        np = p.cloud_off[oid + 1] - p.cloud_off[oid];
+        pts = p.pts + p.cloud_off[oid];
+#pragma unroll
+        for (int t = 0; t < EL_RUNS / 64; ++t)
+          if (EL_RUN * (lane + 64 * t) < np) cs[t] = p.spheres[p.run_off[oid] + lane + 64 * t];
+      }
+      if (oid != last && lane < EL_RUNS / 4) act_w[lane] = 0u;
       last = oid;
     }
-    const bool has = oid >= 0 && oid < p.n_obj;
-    float RL[9], RO[9] = {1.f, 0.f, 0.f, 0.f, 1.f, 0.f, 0.f, 0.f, 1.f}, pO[3] = {0.f, 0.f, 0.f}, pL[3];
+    float RL[9], RO[9], pO[3], pL[3];
     {
-      const float* ls = q.link_state + (int64_t)s * 13 * EL + (int64_t)e * p.L + l;
-      pL[0] = ls[0]; pL[1] = ls[EL]; pL[2] = ls[2 * EL];
-      quat_to_R(ls[3 * EL], ls[4 * EL], ls[5 * EL], ls[6 * EL], RL);
+      float R[9];
+      quat_to_R(pz[3], pz[4], pz[5], pz[6], R);
+#pragma unroll
+      for (int i = 0; i < 9; ++i) {
+        RL[i] = uni(R[i], 0);
+        RO[i] = uni(R[i], 32);
+      }
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        pL[i] = uni(pz[i], 0);
+        pO[i] = uni(pz[i], 32);
+      }
     }
-    if (has && q.obj_state) {
-      const float* os = q.obj_state + (int64_t)s * 13 * p.E + e;
-      pO[0] = os[0]; pO[1] = os[p.E]; pO[2] = os[2 * p.E];
-      quat_to_R(os[3 * p.E], os[4 * p.E], os[5 * p.E], os[6 * p.E], RO);
-    }
+    if (s + 1 < q.n_steps) fetch(s + 1);
     // 2. source probes with h_i > 0
+    if (sg == S) {
+      sg = 0;
+      h = mlane && s + g < q.n_steps ? fmaxf(dn - xj.w, 0.0f) : 0.f;
+      if (h > 0.f) hpow = powf(h, p.alpha);
+      if (mlane && s + S + g < q.n_steps) dn = dep[(int64_t)(s + S) * ET];
+    }
     int nsrc = 0;
     {
-      const float* dep = q.depth + (int64_t)s * ET + (int64_t)e * p.T + j0;
-      float h = 0.f;
-      float4 tx = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (lane < nl) {
-        tx = p.tax[j0 + lane];
-        h = fmaxf(dep[lane] - tx.w, 0.0f);
-      }
-      const bool on = lane < nl && h > 0.f;
+      const bool on = g == sg && h > 0.f;
       const uint64_t bal = __ballot(on);
       if (on) {
-        const int slot = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
-        src_a[slot] = make_float4(tx.x, tx.y, tx.z, h);
-        src_b[slot] = make_float4(powf(h, p.alpha), 0.f, 0.f, 0.f);
+        const int slot = rank_of(bal);
+        buf_a[slot] = make_float4(xj.x, xj.y, xj.z, h);
+        buf_b[slot].x = hpow;
       }
       nsrc = __popcll(bal);
+      ++sg;
     }
     __syncthreads();
     // the marker accumulators, first with the dilation terms of this split
     float y0 = 0.f, y1 = 0.f, y2 = 0.f;
     if (mlane) {
       for (int i = g; i < nsrc; i += S) {
-        const float4 a = src_a[i];
+        const float4 a = buf_a[i];
         float r0, r1, r2;
         tproj(xj.x - a.x, xj.y - a.y, xj.z - a.z, nj.x, nj.y, nj.z, r0, r1, r2);
         const float rr = fmaf(r2, r2, fmaf(r1, r1, r0 * r0));
@@ -165,36 +214,84 @@ __global__ __launch_bounds__(64) void tg_elast_kernel(const ElastParams p, const
         float wk = p.c * gk * p.ginv;
         if (p.c != 1.f) wk = fmaf((1.f - p.c) * p.rinv, 1.0f / (rr + p.eps2), wk);
         wk = wk * a.w;
-        const float ha = src_b[i].x * gk;
+        const float ha = buf_b[i].x * gk;
         y0 = fmaf(p.s_d, fmaf(r0, wk, nj.x * ha), y0);
         y1 = fmaf(p.s_d, fmaf(r1, wk, nj.y * ha), y1);
         y2 = fmaf(p.s_d, fmaf(r2, wk, nj.z * ha), y2);
       }
     }
-    // 3. tracked points, their anchors, and the shear terms through the contact list
-    const int np = has ? p.cloud_off[oid + 1] - p.cloud_off[oid] : 0;
-    const float4* pts = p.pts + (has ? p.cloud_off[oid] : 0);
-    uint32_t near = 0;
-    {
-      const int nch = (np + 63) >> 6;
-      bool nr = false;
-      if (lane < nch) {
-        const float4 cs = p.chunks[p.chunk_off[oid] + lane];
-        float w[3], d[3], zc[3];
-        mat_vec(RO, cs.x, cs.y, cs.z, w);
+    // 3. tracked points, their anchors, and the shear terms through the contact list; the margin
+    // covers the rounding of the positions, which grows with the object's distance from the origin
+    int nrun = 0;
+    const float reach = p.eta_exit + 1e-6f + 5e-7f * (fabsf(pO[0]) + fabsf(pO[1]) + fabsf(pO[2]));
+#pragma unroll
+    for (int t = 0; t < EL_RUNS / 64; ++t) {
+      if (64 * EL_RUN * t >= np) break;   // uniform
+      const int r = lane + 64 * t;
+      bool near = false;
+      if (EL_RUN * r < np) {
+        float w[3], d[3], z[3];
+        mat_vec(RO, cs[t].x, cs[t].y, cs[t].z, w);
 #pragma unroll
         for (int c = 0; c < 3; ++c) d[c] = (w[c] + pO[c]) - pL[c];
-        mat_T_vec(RL, d[0], d[1], d[2], zc);
-        nr = !(pad_sdf(zc[0], zc[1], zc[2], pc, ph) - cs.w > p.eta_exit + 1e-6f);
+        mat_T_vec(RL, d[0], d[1], d[2], z);
+        const float m0 = fmaxf(fabsf(z[0] - pc.x) - ph.x, 0.0f), m1 = fmaxf(fabsf(z[1] - pc.y) - ph.y, 0.0f),
+                    m2 = fmaxf(fabsf(z[2] - pc.z) - ph.z, 0.0f);
+        const float far = cs[t].w + reach;
+        near = !(fmaf(m2, m2, fmaf(m1, m1, m0 * m0)) > far * far * 1.000004f);
+        if (!near) act_b[r] = 0;   // a run out of reach drops its anchors
       }
-      near = (uint32_t)__ballot(nr);
+      const uint64_t bal = __ballot(near);
+      if (near) runs[nrun + rank_of(bal)] = (uint8_t)r;
+      nrun += __popcll(bal);
     }
+    __syncthreads();
     int cnt = 0;
-    auto consume = [&]() {
+    for (int r0 = 0; r0 < nrun; r0 += 64 / EL_RUN) {
+      const int r = r0 + lane / EL_RUN, i = lane % EL_RUN;
+      bool on = false, act = false;
+      float z[3] = {0.f, 0.f, 0.f}, hp = 0.f;
+      float4 anc = make_float4(0.f, 0.f, 0.f, 0.f);
+      int run = 0;
+      if (r < nrun) {
+        run = runs[r];
+        const int idx = EL_RUN * run + i;
+        const bool a = (act_b[run] >> i) & 1u;
+        if (a) anc = anchor[idx];   // asked for with the point, before the position that needs it is known
+        if (idx < np) {
+          const float4 ph4 = pts[idx];
+          float w[3], d[3];
+          mat_vec(RO, ph4.x, ph4.y, ph4.z, w);
+#pragma unroll
+          for (int c = 0; c < 3; ++c) d[c] = (w[c] + pO[c]) - pL[c];
+          mat_T_vec(RL, d[0], d[1], d[2], z);
+          const float phi = pad_sdf(z[0], z[1], z[2], pc, ph);
+          act = a;
+          if (!a && phi < -p.eta_enter) {
+            act = true;
+            anc = make_float4(z[0], z[1], z[2], 0.f);
+            anchor[idx] = anc;
+          } else if (a && phi > p.eta_exit) {
+            act = false;
+          }
+          hp = fmaxf(-phi, 0.0f);
+          on = act && hp > 0.f;
+        }
+      }
+      const uint64_t now = __ballot(act), bal = __ballot(on);
+      if (i == 0 && r < nrun) act_b[run] = (uint8_t)(now >> lane);
+      if (on) {
+        const int slot = cnt + rank_of(bal);
+        buf_a[slot] = make_float4(z[0], z[1], z[2], hp);
+        buf_b[slot] = make_float4(z[0] - anc.x, z[1] - anc.y, z[2] - anc.z, 0.f);
+      }
+      cnt += __popcll(bal);
+      // the list is consumed when the next points might not fit, and at the end
+      if (r0 + 64 / EL_RUN < nrun && cnt + 64 <= EL_LIST) continue;
       __syncthreads();
       if (mlane) {
         for (int i = g; i < cnt; i += S) {
-          const float4 a = lst_a[i], b = lst_b[i];
+          const float4 a = buf_a[i], b = buf_b[i];
           float t0, t1, t2, d0, d1, d2;
           tproj(b.x, b.y, b.z, nj.x, nj.y, nj.z, t0, t1, t2);
           tproj(xj.x - a.x, xj.y - a.y, xj.z - a.z, nj.x, nj.y, nj.z, d0, d1, d2);
@@ -207,58 +304,19 @@ __global__ __launch_bounds__(64) void tg_elast_kernel(const ElastParams p, const
       }
       __syncthreads();
       cnt = 0;
-    };
-#pragma unroll
-    for (int k = 0; k < PPL; ++k) {
-      if (64 * k >= np) break;   // uniform: no points left for any lane
-      if (!((near >> k) & 1u)) {  // uniform: the chunk is far from the pad
-        act &= ~(1u << k);
-        continue;
-      }
-      const int idx = lane + 64 * k;
-      bool on = false;
-      float z[3] = {0.f, 0.f, 0.f}, hp = 0.f;
-      if (idx < np) {
-        const float4 ph4 = pts[idx];
-        float w[3], d[3];
-        mat_vec(RO, ph4.x, ph4.y, ph4.z, w);
-#pragma unroll
-        for (int c = 0; c < 3; ++c) d[c] = (w[c] + pO[c]) - pL[c];
-        mat_T_vec(RL, d[0], d[1], d[2], z);
-        const float phi = pad_sdf(z[0], z[1], z[2], pc, ph);
-        const bool a = (act >> k) & 1u;
-        if (!a && phi < -p.eta_enter) {
-          act |= 1u << k;
-          ax[k] = z[0]; ay[k] = z[1]; az[k] = z[2];
-        } else if (a && phi > p.eta_exit) {
-          act &= ~(1u << k);
-        }
-        hp = fmaxf(-phi, 0.0f);
-        on = ((act >> k) & 1u) && hp > 0.f;
-      }
-      const uint64_t bal = __ballot(on);
-      if (bal) {
-        if (cnt + 64 > EL_LIST) consume();
-        if (on) {
-          const int slot = cnt + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32),
-                                                                __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
-          lst_a[slot] = make_float4(z[0], z[1], z[2], hp);
-          lst_b[slot] = make_float4(z[0] - ax[k], z[1] - ay[k], z[2] - az[k], 0.f);
-        }
-        cnt += __popcll(bal);
-      }
     }
-    if (cnt > 0) consume();
     // 4. the splits meet in LDS, in split order
+    float* const ra = (float*)buf_a;
+    float* const rb = (float*)buf_b;
     if (mlane && g > 0) {
-      red[0][lane] = y0; red[1][lane] = y1; red[2][lane] = y2;
+      ra[lane] = y0; ra[64 + lane] = y1; rb[lane] = y2;
     }
     __syncthreads();
     if (mlane && g == 0) {
       for (int gg = 1; gg < S; ++gg) {
-        y0 += red[0][gg * nl + jj];
-        y1 += red[1][gg * nl + jj];
-        y2 += red[2][gg * nl + jj];
+        y0 += ra[gg * nl + jj];
+        y1 += ra[64 + gg * nl + jj];
+        y2 += rb[gg * nl + jj];
       }
       float* o = q.disp + (int64_t)s * 3 * ET + (int64_t)e * p.T + j0 + jj;
       o[0] = y0;
@@ -267,23 +325,18 @@ __global__ __launch_bounds__(64) void tg_elast_kernel(const ElastParams p, const
     }
     __syncthreads();
   }
-#pragma unroll
-  for (int k = 0; k < PPL; ++k) {
-    const int idx = lane + 64 * k;
-    if (idx < p.max_pts) p.anchor[sl * p.max_pts + idx] = make_float4(ax[k], ay[k], az[k], ((act >> k) & 1u) ? 1.f : 0.f);
-  }
+  if (lane < EL_RUNS / 4) p.active[sl * (EL_RUNS / 4) + lane] = act_w[lane];
   if (lane == 0) p.last_oid[sl] = last;
 }
 
-__global__ void tg_elast_reset_kernel(float4* anchor, int32_t* last_oid, int64_t na, int64_t nl) {
+__global__ void tg_elast_reset_kernel(uint32_t* active, int32_t* last_oid, int64_t na, int64_t nl) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < na) anchor[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (i < na) active[i] = 0u;
   if (i < nl) last_oid[i] = -2;
 }
 
 struct tg_elast {
   ElastParams p{};
-  int ppl = 1;
   std::vector<void*> allocs;
   std::string err;
 };
@@ -303,8 +356,8 @@ hipError_t ealloc(tg_elast* h, T** ptr, size_t n) {
 }
 bool aligned16(const void* ptr) { return ((uintptr_t)ptr & 15u) == 0; }
 hipError_t reset_state(const ElastParams& p, hipStream_t st) {
-  const int64_t nl = (int64_t)p.E * p.Ls, na = nl * p.max_pts, n = std::max(na, nl);
-  hipLaunchKernelGGL(tg_elast_reset_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, p.anchor, p.last_oid,
+  const int64_t nl = (int64_t)p.E * p.Ls, na = nl * (EL_RUNS / 4);
+  hipLaunchKernelGGL(tg_elast_reset_kernel, dim3((unsigned)((na + 255) / 256)), dim3(256), 0, st, p.active, p.last_oid,
                      na, nl);
   return hipGetLastError();
 }
@@ -356,8 +409,8 @@ tg_status tg_elast_create(const tg_elast_config* cfg, tg_elast** out) {
     tax[j] = make_float4(cfg->taxel_pos[3 * j], cfg->taxel_pos[3 * j + 1], cfg->taxel_pos[3 * j + 2], cfg->taxel_radius[j]);
     nrm[j] = make_float4(cfg->taxel_normal[3 * j], cfg->taxel_normal[3 * j + 1], cfg->taxel_normal[3 * j + 2], 0.f);
   }
-  std::vector<int32_t> coff(NO + 1, 0), choff(NO + 1, 0);
-  std::vector<float4> pts, chunks;
+  std::vector<int32_t> coff(NO + 1, 0), roff(NO + 1, 0);
+  std::vector<float4> pts, spheres;
   int max_pts = 1;
   for (int o = 0; o < NO; ++o) {
     const tg_point_cloud& c = cfg->clouds[o];
@@ -374,7 +427,7 @@ tg_status tg_elast_create(const tg_elast_config* cfg, tg_elast** out) {
         hi[k] = i ? std::max(hi[k], (double)x[k]) : x[k];
       }
     }
-    // Morton order (10 bits per axis over the cloud's box), so each run of 64 points is compact
+    // Morton order (10 bits per axis over the cloud's box), so each run of EL_RUN points is compact
     std::vector<std::pair<uint32_t, int>> key(c.num_points);
     for (int i = 0; i < c.num_points; ++i) {
       uint32_t m = 0;
@@ -391,9 +444,9 @@ tg_status tg_elast_create(const tg_elast_config* cfg, tg_elast** out) {
       const float* x = c.points + 3 * (int64_t)key[i].second;
       pts.push_back(make_float4(x[0], x[1], x[2], 0.f));
     }
-    // bounding sphere of each run of 64: centre = mean, radius = farthest point, rounded up
-    for (int b0 = 0; b0 < c.num_points; b0 += 64) {
-      const int b1 = std::min(c.num_points, b0 + 64);
+    // bounding sphere of each run: centre = mean, radius = farthest point, rounded up
+    for (int b0 = 0; b0 < c.num_points; b0 += EL_RUN) {
+      const int b1 = std::min(c.num_points, b0 + EL_RUN);
       double m[3] = {0, 0, 0}, r = 0;
       for (int i = b0; i < b1; ++i) {
         m[0] += pts[base + i].x; m[1] += pts[base + i].y; m[2] += pts[base + i].z;
@@ -405,13 +458,12 @@ tg_status tg_elast_create(const tg_elast_config* cfg, tg_elast** out) {
                      dz = pts[base + i].z - (double)mc[2];
         r = std::max(r, std::sqrt(dx * dx + dy * dy + dz * dz));
       }
-      chunks.push_back(make_float4(mc[0], mc[1], mc[2], (float)(r * (1.0 + 1e-6) + 1e-7)));
+      spheres.push_back(make_float4(mc[0], mc[1], mc[2], (float)(r * (1.0 + 1e-6) + 1e-7)));
     }
     coff[o + 1] = coff[o] + c.num_points;
-    choff[o + 1] = choff[o] + (c.num_points + 63) / 64;
+    roff[o + 1] = roff[o] + (c.num_points + EL_RUN - 1) / EL_RUN;
     max_pts = std::max(max_pts, c.num_points);
   }
-  const int ppl = max_pts <= 256 ? 4 : max_pts <= 512 ? 8 : 16;
   tg_elast* h = new (std::nothrow) tg_elast();
   if (!h) return efail(nullptr, TG_ERR_OUT_OF_MEMORY, "host allocation failed");
   ElastParams& p = h->p;
@@ -422,9 +474,9 @@ tg_status tg_elast_create(const tg_elast_config* cfg, tg_elast** out) {
   p.rinv = (float)(2.0 * (double)cfg->eps);                                       // 1 / rho_bar
   p.eps2 = cfg->eps * cfg->eps;
   p.eta_enter = cfg->eta_enter; p.eta_exit = cfg->eta_exit;
-  h->ppl = ppl;
-  int32_t *dsl = nullptr, *doff = nullptr, *dcoff = nullptr, *dlast = nullptr, *dchoff = nullptr;
-  float4 *dtax = nullptr, *dnrm = nullptr, *dpad = nullptr, *dpts = nullptr, *danc = nullptr, *dch = nullptr;
+  int32_t *dsl = nullptr, *doff = nullptr, *dcoff = nullptr, *dlast = nullptr, *droff = nullptr;
+  float4 *dtax = nullptr, *dnrm = nullptr, *dpad = nullptr, *dpts = nullptr, *danc = nullptr, *dsph = nullptr;
+  uint32_t* dact = nullptr;
   const size_t nanc = (size_t)E * Ls * max_pts;
   hipError_t e = ealloc(h, &dsl, Ls);
   if (e == hipSuccess) e = ealloc(h, &doff, L + 1);
@@ -434,12 +486,13 @@ tg_status tg_elast_create(const tg_elast_config* cfg, tg_elast** out) {
   if (e == hipSuccess) e = ealloc(h, &dcoff, NO + 1);
   if (e == hipSuccess) e = ealloc(h, &dpts, pts.size());
   if (e == hipSuccess) e = ealloc(h, &danc, nanc);
+  if (e == hipSuccess) e = ealloc(h, &dact, (size_t)E * Ls * (EL_RUNS / 4));
   if (e == hipSuccess) e = ealloc(h, &dlast, (size_t)E * Ls);
-  if (e == hipSuccess) e = ealloc(h, &dchoff, NO + 1);
-  if (e == hipSuccess) e = ealloc(h, &dch, chunks.size());
-  if (e == hipSuccess) e = hipMemcpy(dchoff, choff.data(), (NO + 1) * sizeof(int32_t), hipMemcpyHostToDevice);
-  if (e == hipSuccess && !chunks.empty())
-    e = hipMemcpy(dch, chunks.data(), chunks.size() * sizeof(float4), hipMemcpyHostToDevice);
+  if (e == hipSuccess) e = ealloc(h, &droff, NO + 1);
+  if (e == hipSuccess) e = ealloc(h, &dsph, spheres.size());
+  if (e == hipSuccess) e = hipMemcpy(droff, roff.data(), (NO + 1) * sizeof(int32_t), hipMemcpyHostToDevice);
+  if (e == hipSuccess && !spheres.empty())
+    e = hipMemcpy(dsph, spheres.data(), spheres.size() * sizeof(float4), hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemcpy(dsl, sls.data(), Ls * sizeof(int32_t), hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemcpy(doff, off, (L + 1) * sizeof(int32_t), hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemcpy(dtax, tax.data(), T * sizeof(float4), hipMemcpyHostToDevice);
@@ -448,7 +501,7 @@ tg_status tg_elast_create(const tg_elast_config* cfg, tg_elast** out) {
   if (e == hipSuccess) e = hipMemcpy(dcoff, coff.data(), (NO + 1) * sizeof(int32_t), hipMemcpyHostToDevice);
   if (e == hipSuccess && !pts.empty()) e = hipMemcpy(dpts, pts.data(), pts.size() * sizeof(float4), hipMemcpyHostToDevice);
   p.sensor_links = dsl; p.link_off = doff; p.tax = dtax; p.nrm = dnrm; p.pad = dpad; p.cloud_off = dcoff;
-  p.pts = dpts; p.anchor = danc; p.last_oid = dlast; p.chunk_off = dchoff; p.chunks = dch;
+  p.pts = dpts; p.anchor = danc; p.active = dact; p.last_oid = dlast; p.run_off = droff; p.spheres = dsph;
   if (e == hipSuccess) e = reset_state(p, nullptr);
   if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
   if (e != hipSuccess) {
@@ -479,11 +532,7 @@ tg_status tg_elast_rollout(tg_elast* h, const tg_step_inputs* in, const float* d
   q.n_steps = n_steps;
   const dim3 grid((unsigned)(h->p.E * h->p.Ls)), block(64);
   const hipStream_t st = (hipStream_t)hip_stream;
-  switch (h->ppl) {
-    case 4: hipLaunchKernelGGL(tg_elast_kernel<4>, grid, block, 0, st, h->p, q); break;
-    case 8: hipLaunchKernelGGL(tg_elast_kernel<8>, grid, block, 0, st, h->p, q); break;
-    default: hipLaunchKernelGGL(tg_elast_kernel<16>, grid, block, 0, st, h->p, q); break;
-  }
+  hipLaunchKernelGGL(tg_elast_kernel, grid, block, 0, st, h->p, q);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? TG_OK : efail(h, TG_ERR_HIP, hipGetErrorString(e));
 }

@@ -127,6 +127,41 @@ def test_calls_in_a_row_and_reset(torch_cuda):
     print(check(g2[4:], ref2, absum2, sensor_mask(sc)))
 
 
+@pytest.mark.parametrize("points,steps,pad,shift", [
+    (1, 1, 1.0, 0.0), (7, 2, 3.0, 0.0), (9, 4, 3.0, 0.0), (63, 5, 2.0, 0.0), (257, 3, 3.0, 0.0), (513, 11, 1.0, 20.0),
+    (1024, 6, 4.0, 0.0)])
+def test_run_edges(torch_cuda, points, steps, pad, shift):
+    """Clouds about the edges of a run of 8 points and of 64 runs, a last run that is not full, objects
+    of different sizes that change, pads so large that the contact list fills, step counts that are no
+    multiple of a link's splits (1 to 5: 40 to 12 markers), poses far from the origin."""
+    sc, inp, _, _, _ = scene(12, steps, moving=True, seed=4)
+    links = [0] + LINKS
+    sizes = [points, max(1, points // 2), max(1, points - 1), points]
+    base = synth.surface_clouds(sc.grids, 1024, seed=11)
+    clouds = [c[:sizes[i % 4]] for i, c in enumerate(base)]
+    pc, ph = synth.elastomer_pads(sc.layout, links)
+    ph = ph * pad
+    depth = oracle_depth(sc, inp)
+    oid = inp.obj_id.copy()
+    oid[:, 3] = -1
+    oid[steps // 2:, ::2] = (oid[steps // 2:, ::2] + 1) % len(clouds)
+    inp.obj_id = oid
+    inp.link_state[:, :3] += np.float32(shift)
+    inp.obj_state[:, :3] += np.float32(shift)
+    from paper_2606_22332_amd import binding as B
+    el = B.Elastomer(sc, clouds, links, pc, ph)
+    import torch
+    dep = torch.from_numpy(np.ascontiguousarray(depth)).cuda()
+    g = el.rollout(B.to_device(inp), dep).cpu().numpy()
+    el.close()
+    lay = sc.layout
+    ref, absum, st = oracle.elastomer_run(lay.link_offset, lay.pos, lay.normal, lay.radius, links, pc, ph, clouds,
+                                          inp.link_state, inp.obj_id, inp.obj_state, depth)
+    mask = np.zeros(lay.num_taxels, bool)
+    mask[:lay.link_offset[max(links) + 1]] = True
+    print(dict(anchored=int(st["active"].sum()), **check(g, ref, absum, mask)))
+
+
 def test_pipeline_from_the_readout(torch_cuda):
     """The GPU readout's depth into the GPU elastomer, the oracle readout's into the oracle."""
     torch = torch_cuda
