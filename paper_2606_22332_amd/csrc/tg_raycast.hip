@@ -8,21 +8,30 @@
 // fails its test is never loaded; each object's root entry is kept apart.  Triangles are stored
 // in leaf order as (a, b, c, outward unit normal), 64 B each, with the mesh's own index.
 //
-// One thread per (step, env, probe), a block row per step.  The probe's centre and axis in the
-// object frame, then two traversals, each descending into the nearer of
-// two passing children and parking the other on a stack in LDS (one column per thread, so equal
-// stack depths fall in different banks); leaves are tested as soon as their entry passes:
-//   1. the sphere query: children within R - best of the centre, nearer box first; at a leaf the
+// One wave per (step, span of up to 3 x 64 probes), in four passes with the probes that go on packed
+// to the front of an LDS queue in between:
+//   1. a lane a probe: its centre in the object frame; a probe that its object's box does not reach
+//      (half of them in a grasp) writes its zeros and is done;
+//   2. the sphere query: children within R - best of the centre, nearer box first; at a leaf the
 //      closest point of each triangle (Voronoi regions of the triangle, with the hardware
 //      reciprocal: 1 ulp); best penetration R - dist, the square root taken only for a triangle
 //      closer than the bound;
-//   2. the ray query along -a: children the ray enters before the nearest hit so far, nearer
+//   3. a lane a probe again: whether it needs the ray query, which it does not where its centre is
+//      known to be outside (outside the object's box, or on the outer side of the face holding the
+//      closest point), for then its first crossing could only enter the mesh;
+//   4. the ray query along -a: children the ray enters before the nearest hit so far, nearer
 //      entry first; at a leaf the ray-triangle test (Moller-Trumbore, barycentric slack 1e-6);
-//      if the nearest hit leaves the mesh, R + t competes with the sphere's best.  It is skipped
-//      for centres known to be outside (outside the object's box, or on the outer side of the
-//      face holding the closest point), where its first crossing could only enter the mesh.
-// Neighbouring lanes are neighbouring probes of one link, so their traversals visit nearly the
-// same nodes (L2 hits; the meshes are a few hundred KB).
+//      if the nearest hit leaves the mesh, R + t competes with the sphere's best.
+// The traversals park far children on a stack in LDS (one column per lane, so equal stack depths
+// fall in different banks).  They are of very unequal length (none to some dozens of nodes), so a lane
+// that ends one takes the next of the queue (walk below).
+// Bound: vector issue with part of the lanes at work, and the L1's data rate (62% busy): the nodes and
+// triangles come from L1 / L2, the meshes are a few hundred KB.  4096 envs x 200 probes x 16 steps, a
+// third of them in contact: 3.26 ms with a thread a probe, whose instructions had 10 of 64 lanes at
+// work; 2.42 ms with the reached probes packed and lanes refilled for the sphere query, 1.84 ms with
+// the ray query likewise and stacks of 4 bytes an entry (a key beside it, tested again before a
+// record is opened, cost 0.3 ms: its LDS holds fewer waves), 1.36 ms with each kind of step taken until no
+// lane waits for it (until fewer than 24 do: 1.76 ms) and spans of 3 chunks.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -40,8 +49,16 @@ using namespace tg;
 
 namespace {
 thread_local std::string g_ray_create_error;
-constexpr int RC_THREADS = 256;
-constexpr int RC_STACK = 32;
+constexpr int RC_STACK = 32;      // deepest tree
+constexpr int RC_CHUNKS = 3;      // most chunks of 64 probes in a wave's span
+constexpr int RC_QUEUE = 64 * RC_CHUNKS;
+constexpr int RC_REFILL = 8;      // free lanes that take new queries
+// A span of more than one chunk only from here on, about the waves the chip holds: longer spans keep
+// the lanes busy, shorter ones spread a small launch.  200-taxel hands, spans of 1 / 2 / 3 / 4 chunks:
+// 3200 chunks 82 / 99 / 111 / 135 us, 6400 117 / 113 / 136 / 135 us, 12800 192 / 160 / 153 / 146 us,
+// 204800 2012 / 1459 / 1359 / 1508 us (at 4 the queue's LDS costs waves).
+constexpr int RC_WAVES = 4096;
+
 
 struct RayNode {   // a child entry: an interior record's two children are entries 2 r and 2 r + 1
   float4 lo;   // box min; w: the child's record (interior) or its first triangle (leaf), as int bits
@@ -70,7 +87,7 @@ struct RayLaunch {
   float* depth;             // [S][E][T]
   float* normal;            // [S][3][E][T] or null
   int32_t* tri;             // [S][E][T] or null
-  int32_t n_steps;
+  int32_t n_steps, chunks;  // chunks of 64 probes per wave
 };
 
 __device__ __forceinline__ float dot3f(float ax, float ay, float az, float bx, float by, float bz) {
@@ -127,191 +144,356 @@ __device__ float tri_ray(float ox, float oy, float oz, float dx, float dy, float
   const float t = dot3f(e2x, e2y, e2z, qx, qy, qz) * inv;
   return t > 0.f ? t : INFINITY;
 }
-}  // namespace
-
-__global__ __launch_bounds__(RC_THREADS) void tg_ray_kernel(const RayParams p, const RayLaunch q) {
-  __shared__ int32_t stk[RC_STACK * RC_THREADS];   // stk[depth * RC_THREADS + tid]
-  const int tid = threadIdx.x;
-  const int64_t ET = (int64_t)p.E * p.T, EL = (int64_t)p.E * p.L;
-  const int64_t idx = (int64_t)blockIdx.x * RC_THREADS + tid;
-  if (idx >= ET) return;   // (no barrier below: the stack column is the thread's own)
-  const int e = (int)(idx / p.T), j = (int)(idx - (int64_t)e * p.T);
-  const float4 ta = p.tax_a[j], tb = p.tax_b[j];
-  const int l = __float_as_int(tb.w);
-  const float R = ta.w;
-  int32_t* st = stk + tid;
-  // one step per block row (the steps are independent): many more waves than a loop over the
-  // steps in each thread, so the chip fills and the divergent traversals balance out
-  for (int s = blockIdx.y; s < q.n_steps; s += gridDim.y) {
-    float v[7];
-    const float* ls = q.link_state + (int64_t)s * 13 * EL + (int64_t)e * p.L + l;
+// a probe's poses and object of one step
+struct RayPose {
+  float pL[3], RL[9], pO[3], RO[9];
+  int oid;
+};
+__device__ __forceinline__ void load_pose(const RayParams& p, const RayLaunch& q, int s, int e, int l, RayPose& w) {
+  const int64_t EL = (int64_t)p.E * p.L;
+  const float* ls = q.link_state + (int64_t)s * 13 * EL + (int64_t)e * p.L + l;
+  float v[7];
 #pragma unroll
-    for (int c = 0; c < 7; ++c) v[c] = ls[c * EL];
-    float RL[9];
-    quat_to_R(v[3], v[4], v[5], v[6], RL);
-    float x[3], a[3];
-    mat_vec(RL, ta.x, ta.y, ta.z, x);
-    mat_vec(RL, tb.x, tb.y, tb.z, a);
-    const int oid = q.obj_id[(int64_t)s * p.E + e];
-    const bool has = oid >= 0 && oid < p.n_obj;
-    float RO[9] = {1.f, 0.f, 0.f, 0.f, 1.f, 0.f, 0.f, 0.f, 1.f}, pO[3] = {0.f, 0.f, 0.f};
-    if (has && q.obj_state) {
-      const float* os = q.obj_state + (int64_t)s * 13 * p.E + e;
-      pO[0] = os[0]; pO[1] = os[p.E]; pO[2] = os[2 * p.E];
-      quat_to_R(os[3 * p.E], os[4 * p.E], os[5 * p.E], os[6 * p.E], RO);
+  for (int c = 0; c < 7; ++c) v[c] = ls[c * EL];
+#pragma unroll
+  for (int c = 0; c < 3; ++c) w.pL[c] = v[c];
+  quat_to_R(v[3], v[4], v[5], v[6], w.RL);
+  const int oid = q.obj_id[(int64_t)s * p.E + e];
+  w.oid = oid >= 0 && oid < p.n_obj ? oid : -1;
+#pragma unroll
+  for (int c = 0; c < 9; ++c) w.RO[c] = c % 4 == 0 ? 1.f : 0.f;
+  w.pO[0] = w.pO[1] = w.pO[2] = 0.f;
+  if (w.oid >= 0 && q.obj_state) {
+    const float* os = q.obj_state + (int64_t)s * 13 * p.E + e;
+    w.pO[0] = os[0]; w.pO[1] = os[p.E]; w.pO[2] = os[2 * p.E];
+    quat_to_R(os[3 * p.E], os[4 * p.E], os[5 * p.E], os[6 * p.E], w.RO);
+  }
+}
+// squared distance from a point to a child's box
+__device__ __forceinline__ float box_d2(const RayNode& c, const float4& x) {
+  const float ex = fmaxf(fmaxf(c.lo.x - x.x, x.x - c.hi.x), 0.f);
+  const float ey = fmaxf(fmaxf(c.lo.y - x.y, x.y - c.hi.y), 0.f);
+  const float ez = fmaxf(fmaxf(c.lo.z - x.z, x.z - c.hi.z), 0.f);
+  return dot3f(ex, ey, ez, ex, ey, ez);
+}
+__device__ __forceinline__ int rank_of(uint64_t bal) {   // the number of lanes below this one in a ballot
+  return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
+}
+
+// Walks the trees of `count` queries, a lane a query, each as a state machine: an interior record to
+// open (cur), triangles of a leaf to test (tri, ntri), a far child that waits for the near one's
+// leaf (far, nfar, kfar), the stack of parked records.  The wave takes the kind of step that more
+// lanes wait for, and takes it until no lane does; lanes that are done take the next queries.  Each query visits its nodes and
+// triangles in the order in which it would alone: the nearer child (by key) first, a far leaf before
+// a near subtree.  take(i) starts query i and returns its root entry's tags, keys(c0, c1, k0, k1) are
+// the children's keys, pass(k) whether a child of key k can still improve the query, test(t) tests a
+// triangle, done() ends the query.
+template <class Take, class Keys, class Pass, class Test, class Done>
+__device__ __forceinline__ void walk(const RayParams& p, int* st, int count, Take&& take, Keys&& keys, Pass&& pass,
+                                     Test&& test, Done&& done) {
+  float kfar = 0.f;
+  int cur = -1, tri = 0, ntri = 0, far = 0, nfar = -1, sp = 0, next = 0;
+  bool busy = false;
+  for (;;) {
+    if (ntri == 0 && cur < 0) {
+      if (nfar >= 0) {   // (the bound may have shrunk at the near child's leaf)
+        if (pass(kfar)) {
+          if (nfar > 0) { tri = far; ntri = nfar; }
+          else cur = far;
+        }
+        nfar = -1;
+      }
+      if (ntri == 0 && cur < 0 && sp > 0) cur = st[--sp * 64];
     }
-    float best = 0.f;
-    int bt = -1;
-    if (has && R > 0.f) {
-      float qo[3], ao[3];
-      mat_T_vec(RO, (v[0] + x[0]) - pO[0], (v[1] + x[1]) - pO[1], (v[2] + x[2]) - pO[2], qo);
-      mat_T_vec(RO, a[0], a[1], a[2], ao);
-      const RayNode rt = p.root[oid];
-      const float4 root_lo = rt.lo, root_hi = rt.hi;
-      // 1. sphere query: children closer than R - best
-      float lim = R;
-      bool bface = false;
-      auto sphere_tri = [&](int t) {
-        const RayTri tr = p.tris[t];
-        bool face;
-        const float d2 = tri_dist2(qo[0], qo[1], qo[2], tr.a, tr.b, tr.c, face);
-        if (d2 < lim * lim) {   // (the square root only for a deeper triangle)
-          const float pen = R - sqrtf(d2);
-          if (pen > best) {
-            best = pen;
-            bt = t;
-            bface = face;
-            lim = R - best;
+    const bool idle = ntri == 0 && cur < 0 && sp == 0;
+    if (idle && busy) {
+      done();
+      busy = false;
+    }
+    const uint64_t free = __ballot(idle);
+    if (next < count && (__popcll(free) >= RC_REFILL || free == ~0ull)) {
+      const int i = next + rank_of(free);
+      if (idle && i < count) {
+        const int2 root = take(i);
+        busy = true;
+        if (root.y > 0) { tri = root.x; ntri = root.y; }
+        else cur = root.x;
+      }
+      next += __popcll(free);
+    } else if (free == ~0ull) {
+      break;
+    }
+    const int nleaf = __popcll(__ballot(ntri > 0)), nopen = __popcll(__ballot(ntri == 0 && cur >= 0));
+    if (nleaf >= nopen) {
+      while (ntri > 0) {
+        test(tri);
+        ++tri;
+        --ntri;
+      }
+    } else {
+      while (ntri == 0 && cur >= 0) {
+        const RayNode c0 = p.nodes[2 * cur], c1 = p.nodes[2 * cur + 1];
+        float k0, k1;
+        keys(c0, c1, k0, k1);
+        const bool sw = k1 < k0;
+        const float ka = sw ? k1 : k0, kb = sw ? k0 : k1;
+        const int wa = __float_as_int(sw ? c1.lo.w : c0.lo.w), na = __float_as_int(sw ? c1.hi.w : c0.hi.w);
+        const int wb = __float_as_int(sw ? c0.lo.w : c1.lo.w), nb = __float_as_int(sw ? c0.hi.w : c1.hi.w);
+        cur = -1;
+        if (pass(ka)) {
+          const bool both = pass(kb);
+          if (na > 0) {
+            tri = wa;
+            ntri = na;
+            if (both) { far = wb; nfar = nb; kfar = kb; }
+          } else {
+            cur = wa;
+            if (both) {
+              if (nb > 0) { tri = wb; ntri = nb; }
+              else st[sp++ * 64] = wb;   // the host bounds the depth
+            }
           }
         }
-      };
-      auto sphere_leaf = [&](const RayNode& c) {
-        const int w0 = __float_as_int(c.lo.w), cnt = __float_as_int(c.hi.w);
-        for (int k = 0; k < cnt; ++k) sphere_tri(w0 + k);
-      };
-      auto box_d2 = [&](const RayNode& c) {
-        const float ex = fmaxf(fmaxf(c.lo.x - qo[0], qo[0] - c.hi.x), 0.f);
-        const float ey = fmaxf(fmaxf(c.lo.y - qo[1], qo[1] - c.hi.y), 0.f);
-        const float ez = fmaxf(fmaxf(c.lo.z - qo[2], qo[2] - c.hi.z), 0.f);
-        return dot3f(ex, ey, ez, ex, ey, ez);
-      };
-      int sp = 0;
-      int cur = -1;
-      if (box_d2(rt) < lim * lim) {
-        if (__float_as_int(rt.hi.w) > 0) sphere_leaf(rt);
-        else cur = __float_as_int(rt.lo.w);
       }
-      while (cur >= 0) {
-        const RayNode c0 = p.nodes[2 * cur], c1 = p.nodes[2 * cur + 1];
-        const float d0 = box_d2(c0), d1 = box_d2(c1);
-        const bool sw = d1 < d0;
-        const RayNode& na = sw ? c1 : c0;
-        const RayNode& nb = sw ? c0 : c1;
-        const float da = sw ? d1 : d0, db = sw ? d0 : d1;
-        int next = -1;
-        if (da < lim * lim) {
-          if (__float_as_int(na.hi.w) > 0) sphere_leaf(na);
-          else next = __float_as_int(na.lo.w);
+    }
+  }
+}
+// writes one probe's outputs
+__device__ __forceinline__ void put(const RayParams& p, const RayLaunch& q, int s, int idx, const RayPose& w,
+                                    float best, int bt) {
+  const int64_t ET = (int64_t)p.E * p.T, o = (int64_t)s * ET + idx;
+  q.depth[o] = best;
+  float4 n = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (bt >= 0) n = p.tris[bt].n;
+  if (q.tri) q.tri[o] = bt >= 0 ? __float_as_int(p.tris[bt].a.w) : -1;
+  if (q.normal) {
+    float nl[3] = {0.f, 0.f, 0.f};
+    if (bt >= 0) {
+      float nw[3];
+      mat_vec(w.RO, n.x, n.y, n.z, nw);
+      mat_T_vec(w.RL, nw[0], nw[1], nw[2], nl);
+    }
+    float* nm = q.normal + (int64_t)s * 3 * ET + idx;
+    nm[0] = nl[0];
+    nm[ET] = nl[1];
+    nm[2 * ET] = nl[2];
+  }
+}
+}  // namespace
+
+__global__ __launch_bounds__(64, 6) void tg_ray_kernel(const RayParams p, const RayLaunch q) {
+  __shared__ float4 qa[RC_QUEUE];         // the probe's centre in the object frame; R, then the sphere's penetration
+  __shared__ float4 qb[RC_QUEUE];         // its root's tags; the sphere's result; the ray's direction and triangle
+  __shared__ uint8_t item[RC_QUEUE];     // its place in the wave's span
+  extern __shared__ int stk[];           // [depth][64] (node, key)
+  const int lane = threadIdx.x;
+  const int ET = p.E * p.T;
+  const int span0 = (int)blockIdx.x * q.chunks * 64;
+  int* const st = stk + lane;
+  for (int s = blockIdx.y; s < q.n_steps; s += gridDim.y) {
+    int count = 0;
+    for (int k = 0; k < q.chunks; ++k) {
+      if (span0 + 64 * k >= ET) break;   // uniform
+      const int idx = span0 + 64 * k + lane;
+      // 1. the probe's centre; a probe that its object's box does not reach is done
+      float4 x4 = make_float4(0.f, 0.f, 0.f, 0.f);
+      int2 root = make_int2(0, 0);
+      bool in = false;
+      if (idx < ET) {
+        const int e = idx / p.T, j = idx - e * p.T;
+        const float4 ta = p.tax_a[j];
+        RayPose w;
+        load_pose(p, q, s, e, __float_as_int(p.tax_b[j].w), w);
+        if (w.oid >= 0 && ta.w > 0.f) {
+          float x[3], qo[3];
+          mat_vec(w.RL, ta.x, ta.y, ta.z, x);
+          mat_T_vec(w.RO, (w.pL[0] + x[0]) - w.pO[0], (w.pL[1] + x[1]) - w.pO[1], (w.pL[2] + x[2]) - w.pO[2], qo);
+          x4 = make_float4(qo[0], qo[1], qo[2], ta.w);
+          const RayNode rt = p.root[w.oid];
+          root = make_int2(__float_as_int(rt.lo.w), __float_as_int(rt.hi.w));
+          in = box_d2(rt, x4) < ta.w * ta.w;
         }
-        if (db < lim * lim) {   // (lim may have shrunk at the first child's leaf)
-          if (__float_as_int(nb.hi.w) > 0) sphere_leaf(nb);
-          else if (next < 0) next = __float_as_int(nb.lo.w);
-          else st[sp++ * RC_THREADS] = __float_as_int(nb.lo.w);   // the host bounds the depth
-        }
-        if (next < 0 && sp > 0) next = st[--sp * RC_THREADS];
-        cur = next;
+        if (!in) put(p, q, s, idx, w, 0.f, -1);
       }
-      // 2. ray query along -a: the nearest crossing.  It can only count when the centre is inside
-      //    the mesh, so it is skipped when the centre is outside the object's box, or when its
-      //    closest point lies inside a face and the centre is on that face's outer side (then the
-      //    ray's first crossing enters the mesh).  Near the surface, where rounding could flip
-      //    that side, the two tests agree to twice the centre's distance from the face.
-      bool outside = !(qo[0] >= root_lo.x && qo[0] <= root_hi.x && qo[1] >= root_lo.y && qo[1] <= root_hi.y &&
-                       qo[2] >= root_lo.z && qo[2] <= root_hi.z);
-      if (!outside && bt >= 0 && bface) {
-        const RayTri tr = p.tris[bt];
-        outside = dot3f(qo[0] - tr.a.x, qo[1] - tr.a.y, qo[2] - tr.a.z, tr.n.x, tr.n.y, tr.n.z) > 0.f;
+      const uint64_t bal = __ballot(in);
+      if (in) {
+        const int slot = count + rank_of(bal);
+        qa[slot] = x4;
+        qb[slot].x = __int_as_float(root.x);
+        qb[slot].y = __int_as_float(root.y);
+        item[slot] = (uint8_t)(64 * k + lane);
       }
-      const float dx = -ao[0], dy = -ao[1], dz = -ao[2];
-      const float ix = 1.0f / dx, iy = 1.0f / dy, iz = 1.0f / dz;
-      float tmin = INFINITY;
-      int th = -1;
-      auto ray_tri = [&](int k) {
-        const RayTri tr = p.tris[k];
-        const float t = tri_ray(qo[0], qo[1], qo[2], dx, dy, dz, tr.a, tr.b, tr.c);
-        if (t < tmin) {
-          tmin = t;
-          th = k;
+      count += __popcll(bal);
+    }
+    __syncthreads();
+
+    // 2. sphere queries: children closer than R - best, nearer box first
+    {
+      float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
+      float best = 0.f, lim = 0.f;
+      int bt = -1, slot = 0;
+      bool bface = false;
+      walk(p, st, count,
+           [&](int i) {
+             slot = i;
+             x = qa[i];
+             best = 0.f;
+             lim = x.w;
+             bt = -1;
+             bface = false;
+             return make_int2(__float_as_int(qb[i].x), __float_as_int(qb[i].y));
+           },
+           [&](const RayNode& c0, const RayNode& c1, float& k0, float& k1) {
+             k0 = box_d2(c0, x);
+             k1 = box_d2(c1, x);
+           },
+           [&](float k) { return k < lim * lim; },
+           [&](int t) {
+             const RayTri tr = p.tris[t];
+             bool face;
+             const float d2 = tri_dist2(x.x, x.y, x.z, tr.a, tr.b, tr.c, face);
+             if (d2 < lim * lim) {   // (the square root only for a deeper triangle)
+               const float pen = x.w - sqrtf(d2);
+               if (pen > best) {
+                 best = pen;
+                 bt = t;
+                 bface = face;
+                 lim = x.w - best;
+               }
+             }
+           },
+           [&]() {
+             qb[slot].x = bface ? -best : best;   // (a penetration on a face is positive)
+             qb[slot].y = __int_as_float(bt);
+           });
+    }
+    __syncthreads();
+
+    // 3. the ray query along -a can only count when the centre is inside the mesh, so it is
+    //    skipped when the centre is outside the object's box, or when its closest point lies
+    //    inside a face and the centre is on that face's outer side (then the ray's first crossing
+    //    enters the mesh).  Near the surface, where rounding could flip that side, the two tests
+    //    agree to twice the centre's distance from the face.  The probes that need one move to the
+    //    front of the queue.
+    int rays = 0;
+    for (int i0 = 0; i0 < count; i0 += 64) {
+      const int i = i0 + lane;
+      bool need = false;
+      float4 x = make_float4(0.f, 0.f, 0.f, 0.f), d = x;
+      int it = 0;
+      if (i < count) {
+        it = item[i];
+        const int idx = span0 + it, e = idx / p.T;
+        const float4 tb = p.tax_b[idx - e * p.T];
+        RayPose w;
+        load_pose(p, q, s, e, __float_as_int(tb.w), w);
+        x = qa[i];
+        const float res = qb[i].x;
+        const int bt = __float_as_int(qb[i].y);
+        const RayNode rt = p.root[w.oid];
+        need = x.x >= rt.lo.x && x.x <= rt.hi.x && x.y >= rt.lo.y && x.y <= rt.hi.y && x.z >= rt.lo.z && x.z <= rt.hi.z;
+        if (need && bt >= 0 && res < 0.f) {
+          const RayTri tr = p.tris[bt];
+          need = !(dot3f(x.x - tr.a.x, x.y - tr.a.y, x.z - tr.a.z, tr.n.x, tr.n.y, tr.n.z) > 0.f);
         }
-      };
-      auto ray_leaf = [&](const RayNode& c) {
-        const int w0 = __float_as_int(c.lo.w), cnt = __float_as_int(c.hi.w);
-        for (int k = 0; k < cnt; ++k) ray_tri(w0 + k);
-      };
-      // entry parameter of the ray into a box, or +inf when it misses it before tmin
+        if (need) {
+          float a[3], ao[3];
+          mat_vec(w.RL, tb.x, tb.y, tb.z, a);
+          mat_T_vec(w.RO, a[0], a[1], a[2], ao);
+          x.w = fabsf(res);
+          d = make_float4(-ao[0], -ao[1], -ao[2], __int_as_float(bt));
+        } else {
+          put(p, q, s, idx, w, fabsf(res), bt);
+        }
+      }
+      __syncthreads();
+      const uint64_t bal = __ballot(need);
+      if (need) {
+        const int slot = rays + rank_of(bal);   // (at most i: every lane has read its own)
+        qa[slot] = x;
+        qb[slot] = d;
+        item[slot] = (uint8_t)it;
+      }
+      rays += __popcll(bal);
+    }
+    __syncthreads();
+    //    children the ray enters before the nearest hit so far, nearer entry first
+    {
+      float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
+      float dx = 0.f, dy = 0.f, dz = 0.f, ix = 0.f, iy = 0.f, iz = 0.f, tmin = INFINITY;
+      int th = -1, slot = 0;
+      // entry parameter of the ray into a box, or +inf when it misses it
       auto box_t = [&](const RayNode& c) {
-        const float t1x = (c.lo.x - qo[0]) * ix, t2x = (c.hi.x - qo[0]) * ix;
-        const float t1y = (c.lo.y - qo[1]) * iy, t2y = (c.hi.y - qo[1]) * iy;
-        const float t1z = (c.lo.z - qo[2]) * iz, t2z = (c.hi.z - qo[2]) * iz;
+        const float t1x = (c.lo.x - x.x) * ix, t2x = (c.hi.x - x.x) * ix;
+        const float t1y = (c.lo.y - x.y) * iy, t2y = (c.hi.y - x.y) * iy;
+        const float t1z = (c.lo.z - x.z) * iz, t2z = (c.hi.z - x.z) * iz;
         const float tn = fmaxf(fmaxf(fminf(t1x, t2x), fminf(t1y, t2y)), fmaxf(fminf(t1z, t2z), 0.f));
         const float tf = fminf(fminf(fmaxf(t1x, t2x), fmaxf(t1y, t2y)), fminf(fmaxf(t1z, t2z), tmin));
         return tn <= tf ? tn : INFINITY;
       };
-      sp = 0;
-      cur = -1;
-      if (!outside && box_t(rt) < INFINITY) {
-        if (__float_as_int(rt.hi.w) > 0) ray_leaf(rt);
-        else cur = __float_as_int(rt.lo.w);
-      }
-      while (cur >= 0) {
-        const RayNode c0 = p.nodes[2 * cur], c1 = p.nodes[2 * cur + 1];
-        const float t0 = box_t(c0), t1 = box_t(c1);
-        const bool sw = t1 < t0;
-        const RayNode& na = sw ? c1 : c0;
-        const RayNode& nb = sw ? c0 : c1;
-        const float ta_ = sw ? t1 : t0;
-        int next = -1;
-        if (ta_ < INFINITY) {
-          if (__float_as_int(na.hi.w) > 0) ray_leaf(na);
-          else next = __float_as_int(na.lo.w);
-        }
-        if (box_t(nb) < INFINITY) {   // (re-tested: tmin may have shrunk at the first child's leaf)
-          if (__float_as_int(nb.hi.w) > 0) ray_leaf(nb);
-          else if (next < 0) next = __float_as_int(nb.lo.w);
-          else st[sp++ * RC_THREADS] = __float_as_int(nb.lo.w);
-        }
-        if (next < 0 && sp > 0) next = st[--sp * RC_THREADS];
-        cur = next;
-      }
-      if (th >= 0) {
-        const float4 n = p.tris[th].n;
-        if (dot3f(dx, dy, dz, n.x, n.y, n.z) > 0.f && R + tmin > best) {
-          best = R + tmin;
-          bt = th;
-        }
-      }
+      walk(p, st, rays,
+           [&](int i) {
+             slot = i;
+             x = qa[i];
+             dx = qb[i].x;
+             dy = qb[i].y;
+             dz = qb[i].z;
+             ix = 1.0f / dx;
+             iy = 1.0f / dy;
+             iz = 1.0f / dz;
+             tmin = INFINITY;
+             th = -1;
+             const int e = (span0 + item[i]) / p.T;
+             const RayNode rt = p.root[q.obj_id[(int64_t)s * p.E + e]];
+             int2 root = make_int2(__float_as_int(rt.lo.w), __float_as_int(rt.hi.w));
+             if (!(box_t(rt) < INFINITY)) root = make_int2(-1, 0);
+             return root;
+           },
+           [&](const RayNode& c0, const RayNode& c1, float& k0, float& k1) {
+             k0 = box_t(c0);
+             k1 = box_t(c1);
+           },
+           [&](float k) { return k <= tmin && k < INFINITY; },
+           [&](int t) {
+             const RayTri tr = p.tris[t];
+             const float tt = tri_ray(x.x, x.y, x.z, dx, dy, dz, tr.a, tr.b, tr.c);
+             if (tt < tmin) {
+               tmin = tt;
+               th = t;
+             }
+           },
+           [&]() {   // a hit that leaves the mesh
+             bool out = false;
+             if (th >= 0) {
+               const float4 n = p.tris[th].n;
+               out = dot3f(dx, dy, dz, n.x, n.y, n.z) > 0.f;
+             }
+             qb[slot].x = out ? tmin : -1.f;
+             qb[slot].y = __int_as_float(th);
+           });
     }
-    const int64_t o = (int64_t)s * ET + idx;
-    q.depth[o] = best;
-    if (q.tri) q.tri[o] = bt >= 0 ? __float_as_int(p.tris[bt].a.w) : -1;
-    if (q.normal) {
-      float nl[3] = {0.f, 0.f, 0.f};
-      if (bt >= 0) {
-        const float4 n = p.tris[bt].n;
-        float nw[3];
-        mat_vec(RO, n.x, n.y, n.z, nw);
-        mat_T_vec(RL, nw[0], nw[1], nw[2], nl);
+    __syncthreads();
+    for (int i = lane; i < rays; i += 64) {
+      const int idx = span0 + item[i], e = idx / p.T, j = idx - e * p.T;
+      RayPose w;
+      load_pose(p, q, s, e, __float_as_int(p.tax_b[j].w), w);
+      const float4 b = qb[i];
+      const float R = p.tax_a[j].w;
+      float best = qa[i].w;
+      int bt = __float_as_int(b.w);
+      if (b.x >= 0.f && R + b.x > best) {
+        best = R + b.x;
+        bt = __float_as_int(b.y);
       }
-      float* nm = q.normal + (int64_t)s * 3 * ET + idx;
-      nm[0] = nl[0];
-      nm[ET] = nl[1];
-      nm[2 * ET] = nl[2];
+      put(p, q, s, idx, w, best, bt);
     }
+    __syncthreads();
   }
 }
 
 struct tg_ray {
   RayParams p{};
+  int depth = 1;   // of the deepest tree: a walk parks at most one record a level
   std::vector<void*> allocs;
   std::string err;
 };
@@ -447,6 +629,7 @@ tg_status tg_ray_create(const tg_ray_config* cfg, tg_ray** out) {
   std::vector<RayNode> nodes;
   std::vector<RayTri> tris;
   std::vector<RayNode> roots(NO);
+  int depth = 1;
   for (int o = 0; o < NO; ++o) {
     const tg_mesh& m = cfg->meshes[o];
     if (m.num_verts < 3 || m.num_tris < 1 || !m.verts || !m.tris)
@@ -477,9 +660,11 @@ tg_status tg_ray_create(const tg_ray_config* cfg, tg_ray** out) {
     }
     roots[o] = bd.build(0, m.num_tris, 0);
     if (bd.max_depth + 2 > RC_STACK) return rfail(nullptr, TG_ERR_UNSUPPORTED, "BVH deeper than the traversal stack");
+    depth = std::max(depth, bd.max_depth);
   }
   tg_ray* h = new (std::nothrow) tg_ray();
   if (!h) return rfail(nullptr, TG_ERR_OUT_OF_MEMORY, "host allocation failed");
+  h->depth = depth;
   RayParams& p = h->p;
   p.E = E; p.L = L; p.T = T; p.n_obj = NO;
   float4 *dta = nullptr, *dtb = nullptr;
@@ -525,9 +710,10 @@ tg_status tg_ray_rollout(tg_ray* h, const tg_step_inputs* in, float* depth, floa
   q.normal = normal;
   q.tri = tri;
   q.n_steps = n_steps;
-  const int64_t ET = (int64_t)h->p.E * h->p.T;
-  hipLaunchKernelGGL(tg_ray_kernel, dim3((unsigned)((ET + RC_THREADS - 1) / RC_THREADS), (unsigned)std::min(n_steps, 65535)), dim3(RC_THREADS), 0,
-                     (hipStream_t)hip_stream, h->p, q);
+  const int64_t chunks = ((int64_t)h->p.E * h->p.T + 63) / 64, rows = std::min(n_steps, 65535);
+  q.chunks = (int)std::min<int64_t>(RC_CHUNKS, std::max<int64_t>(1, chunks * rows / RC_WAVES));
+  const dim3 grid((unsigned)((chunks + q.chunks - 1) / q.chunks), (unsigned)rows);
+  hipLaunchKernelGGL(tg_ray_kernel, grid, dim3(64), h->depth * 64 * sizeof(int), (hipStream_t)hip_stream, h->p, q);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? TG_OK : rfail(h, TG_ERR_HIP, hipGetErrorString(e));
 }

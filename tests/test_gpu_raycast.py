@@ -147,6 +147,41 @@ def test_full_size_sampled(torch_cuda):
     print(check(g, ref, sc_sub, sub, meshes))
 
 
+@pytest.mark.parametrize("envs,steps", [(1, 1), (332, 3), (332, 8), (332, 13)])
+def test_spans(torch_cuda, envs, steps):
+    """Launches whose waves take spans of 1, 2 and 3 chunks of probes (332 x 200 probes are 1038 chunks a
+    step, the last one not full), with trees that are one leaf and one record: each step equals the
+    step launched alone, bit for bit, with and without the optional outputs, and sampled envs the oracle."""
+    torch = torch_cuda
+    from paper_2606_22332_amd import binding as B
+    sc = synth.make_scene("c2", num_envs=envs, num_steps=steps)
+    inp = synth.make_inputs(sc)
+    inp.obj_state = synth.random_object_state(sc, steps)
+    inp.obj_id = np.arange(envs, dtype=np.int32)[None].repeat(steps, 0) % 9 - 1 if envs > 1 else inp.obj_id
+    meshes = synth.object_meshes(sc.grids)
+    v = np.array([[1, 1, 1], [1, -1, -1], [-1, 1, -1], [-1, -1, 1]], np.float32) * np.float32(0.04)
+    meshes[1] = (v, np.array([[0, 1, 2], [0, 3, 1], [0, 2, 3], [1, 3, 2]], np.int32))
+    o = np.concatenate([np.eye(3), -np.eye(3)]).astype(np.float32) * np.float32(0.05)
+    meshes[2] = (o, np.array([[0, 1, 2], [1, 3, 2], [3, 4, 2], [4, 0, 2], [1, 0, 5], [3, 1, 5], [4, 3, 5], [0, 4, 5]],
+                             np.int32))
+    rc = B.Raycast(sc, meshes)
+    d = B.to_device(inp)
+    dep, nm, tri = rc.rollout(d)
+    for s in range(steps):
+        d1, n1, t1 = rc.rollout(d, n_steps=1, s_in=s)
+        assert torch.equal(d1[0], dep[s]) and torch.equal(n1[0], nm[s]) and torch.equal(t1[0], tri[s])
+    only, no_n, no_t = rc.rollout(d, want_normal=False, want_tri=False)
+    assert torch.equal(only, dep) and no_n is None and no_t is None
+    rc.close()
+    pick = np.unique(np.array([0, 1, 2, 3, 12, 299, 331]) % envs)
+    idx = torch.as_tensor(pick, device="cuda")
+    g = (dep[:, idx].cpu().numpy(), nm[:, :, idx].cpu().numpy(), tri[:, idx].cpu().numpy())
+    sub = synth.subset_envs(inp, pick, sc.layout.num_links)
+    sc_sub = synth.make_scene("c2", num_envs=len(pick))
+    ref = run_oracle(sc_sub, sub, meshes, tri_query=g[2])
+    print(check(g, ref, sc_sub, sub, meshes))
+
+
 def test_rejects_bad_meshes(torch_cuda):
     from paper_2606_22332_amd import binding as B
     sc = synth.make_scene("c2", num_envs=2, num_steps=1)
