@@ -183,11 +183,11 @@ __device__ __forceinline__ int rank_of(uint64_t bal) {   // the number of lanes 
 // Walks the trees of `count` queries, a lane a query, each as a state machine: an interior record to
 // open (cur), triangles of a leaf to test (tri, ntri), a far child that waits for the near one's
 // leaf (far, nfar, kfar), the stack of parked records.  The wave takes the kind of step that more
-// lanes wait for, and takes it until no lane does; lanes that are done take the next queries.  Each query visits its nodes and
-// triangles in the order in which it would alone: the nearer child (by key) first, a far leaf before
-// a near subtree.  take(i) starts query i and returns its root entry's tags, keys(c0, c1, k0, k1) are
-// the children's keys, pass(k) whether a child of key k can still improve the query, test(t) tests a
-// triangle, done() ends the query.
+// lanes wait for, and takes it until no lane does; lanes that are done take the next queries.  Each
+// query visits its nodes and triangles in the order in which it would alone: the nearer child (by
+// key) first, a far leaf before a near subtree.  take(i) starts query i and returns its root entry's
+// tags, keys(c0, c1, k0, k1) are the children's keys, pass(k) whether a child of key k can still
+// improve the query, test(t) tests a triangle, done() ends the query.
 template <class Take, class Keys, class Pass, class Test, class Done>
 __device__ __forceinline__ void walk(const RayParams& p, int* st, int count, Take&& take, Keys&& keys, Pass&& pass,
                                      Test&& test, Done&& done) {
@@ -284,8 +284,8 @@ __device__ __forceinline__ void put(const RayParams& p, const RayLaunch& q, int 
 __global__ __launch_bounds__(64, 6) void tg_ray_kernel(const RayParams p, const RayLaunch q) {
   __shared__ float4 qa[RC_QUEUE];         // the probe's centre in the object frame; R, then the sphere's penetration
   __shared__ float4 qb[RC_QUEUE];         // its root's tags; the sphere's result; the ray's direction and triangle
-  __shared__ uint8_t item[RC_QUEUE];     // its place in the wave's span
-  extern __shared__ int stk[];           // [depth][64] (node, key)
+  __shared__ uint8_t item[RC_QUEUE];      // its place in the wave's span
+  extern __shared__ int stk[];            // [depth][64] parked records
   const int lane = threadIdx.x;
   const int ET = p.E * p.T;
   const int span0 = (int)blockIdx.x * q.chunks * 64;
