@@ -11,10 +11,13 @@
 
 namespace tg {
 
-// A cubic SDF grid of n^3 samples.  The readout stores it in bricks of 4 x 4 x 4 values (256 B):
-// sample (x, y, z) lives at offset + ((z/4 * nb + y/4) * nb + x/4) * 64 + (z%4 * 4 + y%4) * 4 + x%4,
-// nb = ceil(n/4), so the 8 corners of a cell fall in one or two 128-byte lines and neighbouring
-// probes of a patch share bricks.  (The training-target kernels keep plain x-fastest order, nb = 0.)
+// A cubic SDF grid of n^3 samples.  The readout stores it in bricks of 3 x 3 x 3 cells with all their
+// corners, 4 x 4 x 4 values (256 B): cell (x, y, z) lies in brick offset / 64 + ((z/3 * nb + y/3) * nb + x/3)
+// at (z%3 * 4 + y%3) * 4 + x%3, nb = ceil((n - 1) / 3).  Neighbouring bricks repeat the values they
+// share (2.3 times the samples at n = 64), so a lookup has one address, four 8-byte loads and one or two
+// 128-byte lines.  Against bricks of 4 x 4 x 4 samples, whose cells reach into up to 8 bricks, with eight
+// loads: the 20480-env dense rollout of 16 steps 14.45 -> 14.05 ms, the 1024-env thermal one 1.92 -> 1.90.
+// (The training-target kernels keep plain x-fastest order, nb = 0.)
 struct GridDesc {
   float origin[3];
   float spacing;
@@ -22,7 +25,7 @@ struct GridDesc {
   float nm1;       // (float)(n - 1)
   int32_t n;
   int32_t nb;      // bricks per axis
-  int64_t offset;  // first value (a brick boundary) in the concatenated grid buffer
+  int64_t offset;  // first value (a multiple of 64 here) in the concatenated grid buffer
 };
 
 struct Pose {     // rotation, position, velocity, angular velocity

@@ -141,26 +141,19 @@ __device__ __forceinline__ void grid_lookup(const GridDesc& g, const float* grid
     ii[i] = k;
     h.t[i] = uc[i] - (float)k;
   }
-  // Brick addressing, separable per axis (element units): x -> (x/4)*64 + x%4,
-  // y -> (y/4)*64nb + (y%4)*4, z -> (z/4)*64nb^2 + (z%4)*16; the +1 corner steps into the next
-  // brick when the cell sits on a brick's last row.  32-bit byte offsets from the uniform base of
-  // all grids, so the loads use a scalar base.
+  // The cell's brick and place in it (x / 3 by multiplication, exact below 2^16).  A brick holds all
+  // 8 corners, so one address and four 8-byte loads at fixed distances fetch them.
   const uint32_t nb = (uint32_t)g.nb;
   const uint32_t x0 = (uint32_t)ii[0], y0 = (uint32_t)ii[1], z0 = (uint32_t)ii[2];
-  const uint32_t sy = nb << 6, sz = sy * nb;
-  const uint32_t ax0 = ((x0 >> 2) << 6) + (x0 & 3u);
-  const uint32_t ax1 = ax0 + ((x0 & 3u) == 3u ? 61u : 1u);
-  const uint32_t ay0 = (y0 >> 2) * sy + ((y0 & 3u) << 2);
-  const uint32_t ay1 = ay0 + ((y0 & 3u) == 3u ? sy - 12u : 4u);
-  const uint32_t az0 = (z0 >> 2) * sz + ((z0 & 3u) << 4);
-  const uint32_t az1 = az0 + ((z0 & 3u) == 3u ? sz - 48u : 16u);
-  const uint32_t base = (uint32_t)g.offset;
-  const uint32_t r00 = base + ay0 + az0, r10 = base + ay1 + az0, r01 = base + ay0 + az1, r11 = base + ay1 + az1;
-  const char* Gb = (const char*)grid_vals;
-  h.c000 = *(const float*)(Gb + (r00 + ax0) * 4u); h.c100 = *(const float*)(Gb + (r00 + ax1) * 4u);
-  h.c010 = *(const float*)(Gb + (r10 + ax0) * 4u); h.c110 = *(const float*)(Gb + (r10 + ax1) * 4u);
-  h.c001 = *(const float*)(Gb + (r01 + ax0) * 4u); h.c101 = *(const float*)(Gb + (r01 + ax1) * 4u);
-  h.c011 = *(const float*)(Gb + (r11 + ax0) * 4u); h.c111 = *(const float*)(Gb + (r11 + ax1) * 4u);
+  const uint32_t bx = (x0 * 43691u) >> 17, by = (y0 * 43691u) >> 17, bz = (z0 * 43691u) >> 17;
+  const uint32_t brick = (uint32_t)(g.offset >> 6) + (bz * nb + by) * nb + bx;
+  const uint32_t cell = ((z0 - 3u * bz) * 4u + (y0 - 3u * by)) * 4u + (x0 - 3u * bx);
+  const char* c0 = (const char*)grid_vals + (uint64_t)brick * 256u + cell * 4u;
+  typedef float pair __attribute__((ext_vector_type(2), aligned(4)));
+  const pair r00 = *(const pair*)c0, r10 = *(const pair*)(c0 + 16), r01 = *(const pair*)(c0 + 64),
+             r11 = *(const pair*)(c0 + 80);
+  h.c000 = r00.x; h.c100 = r00.y; h.c010 = r10.x; h.c110 = r10.y;
+  h.c001 = r01.x; h.c101 = r01.y; h.c011 = r11.x; h.c111 = r11.y;
   const float* t = h.t;
   const float l00 = lerpf(t[0], h.c000, h.c100), l10 = lerpf(t[0], h.c010, h.c110);
   const float l01 = lerpf(t[0], h.c001, h.c101), l11 = lerpf(t[0], h.c011, h.c111);

@@ -28,22 +28,24 @@ thread_local std::string g_create_error;
 
 inline int32_t align16i(int64_t x) { return (int32_t)((x + 15) & ~int64_t(15)); }
 
-// Values of an n^3 grid in 4 x 4 x 4 bricks (the layout GridDesc describes), zero padded.
+// Values of an n^3 grid in bricks of 3 x 3 x 3 cells (the layout GridDesc describes), zero padded.
 inline int64_t brick_values(int n) {
-  const int64_t nb = (n + 3) / 4;
+  const int64_t nb = (n + 1) / 3;
   return nb * nb * nb * 64;
-}
-void to_bricks(const float* v, int n, float* out) {
-  const int nb = (n + 3) / 4;
-  for (int z = 0; z < n; ++z)
-    for (int y = 0; y < n; ++y)
-      for (int x = 0; x < n; ++x) {
-        const int64_t b = ((int64_t)(z >> 2) * nb + (y >> 2)) * nb + (x >> 2);
-        out[b * 64 + ((z & 3) * 4 + (y & 3)) * 4 + (x & 3)] = v[((int64_t)z * n + y) * n + x];
-      }
 }
 
 }  // namespace
+
+// The bricks of an n^3 grid from its samples in x-fastest order, a thread a value.  (On the host this
+// took longer than the rest of create.)
+__global__ void tg_brick_kernel(const float* v, int n, float* out) {
+  const uint32_t nb = (uint32_t)(n + 1) / 3u;
+  const uint32_t b = blockIdx.x * 4u + (threadIdx.x >> 6), c = threadIdx.x & 63u;
+  const uint32_t bz = b / (nb * nb), by = b / nb - bz * nb, bx = b - (bz * nb + by) * nb;
+  if (bz >= nb) return;
+  const int z = (int)(3u * bz + (c >> 4)), y = (int)(3u * by + ((c >> 2) & 3u)), x = (int)(3u * bx + (c & 3u));
+  out[(int64_t)b * 64 + c] = z < n && y < n && x < n ? v[((int64_t)z * n + y) * n + x] : 0.f;
+}
 
 // Episode reset: zero the dynamic state and draw dead flag, stuck value and gain with
 // counter (env, taxel, reset step, 7).
@@ -449,9 +451,13 @@ tg_status tg_readout_create(const tg_readout_config* cfg, tg_readout** out) {
   h->noise = noise;
   h->xt = noise ? nz.xtalk_kind : 0;
   h->hy = noise ? nz.hyst_mode : 0;
-  int64_t total_vals = 0;   // bricked: ceil(n/4)^3 bricks of 64 values per grid
-  for (int g = 0; g < NO; ++g) total_vals += brick_values(cfg->grids[g].n);
-  if (total_vals * 4 > (int64_t)0xffffffffLL) {   // grid corners are addressed with 32-bit byte offsets
+  int64_t total_vals = 0, samples = 0;   // samples: with each axis rounded up to a multiple of 4
+  for (int g = 0; g < NO; ++g) {
+    const int64_t n4 = (cfg->grids[g].n + 3) / 4 * 4;
+    samples += n4 * n4 * n4;
+    total_vals += brick_values(cfg->grids[g].n);
+  }
+  if (samples * 4 > (int64_t)0xffffffffLL) {   // (the bricks hold up to 2.4 times as many)
     delete h;
     return fail(nullptr, TG_ERR_UNSUPPORTED, "grid values exceed 4 GiB");
   }
@@ -478,7 +484,7 @@ tg_status tg_readout_create(const tg_readout_config* cfg, tg_readout** out) {
     gd[g].hinv = one / G.spacing;
     gd[g].nm1 = (float)(G.n - 1);
     gd[g].n = G.n;
-    gd[g].nb = (G.n + 3) / 4;
+    gd[g].nb = (G.n + 1) / 3;
     gd[g].offset = goff;
     goff += brick_values(G.n);
   }
@@ -524,12 +530,21 @@ tg_status tg_readout_create(const tg_readout_config* cfg, tg_readout** out) {
   if (e == hipSuccess) e = hipMemcpy(dB, tB.data(), T * sizeof(float4), hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemcpy(dOff, off, (L + 1) * sizeof(int32_t), hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipMemcpy(dG, gd.data(), NO * sizeof(GridDesc), hipMemcpyHostToDevice);
+  int nmax = 0;
+  for (int g = 0; g < NO; ++g) nmax = std::max(nmax, (int)cfg->grids[g].n);
+  float* raw = nullptr;   // one grid's samples at a time
+  if (e == hipSuccess && NO > 0) e = hipMalloc((void**)&raw, (size_t)nmax * nmax * nmax * sizeof(float));
   for (int g = 0; g < NO && e == hipSuccess; ++g) {
     const tg_sdf_grid& G = cfg->grids[g];
-    std::vector<float> bricks((size_t)brick_values(G.n), 0.f);
-    to_bricks(G.values, G.n, bricks.data());
-    e = hipMemcpy(dV + gd[g].offset, bricks.data(), bricks.size() * sizeof(float), hipMemcpyHostToDevice);
+    e = hipMemcpy(raw, G.values, (size_t)G.n * G.n * G.n * sizeof(float), hipMemcpyHostToDevice);
+    if (e != hipSuccess) break;
+    const int64_t bricks = brick_values(G.n) / 64;
+    hipLaunchKernelGGL(tg_brick_kernel, dim3((unsigned)((bricks + 3) / 4)), dim3(256), 0, nullptr, raw, G.n,
+                       dV + gd[g].offset);
+    e = hipGetLastError();
   }
+  if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+  if (raw) (void)hipFree(raw);
   if (e != hipSuccess) {
     tg_readout_destroy(h);
     return fail(nullptr, TG_ERR_HIP, std::string("hipMemcpy: ") + hipGetErrorString(e));

@@ -454,6 +454,21 @@ def test_zero_step_rollout_is_a_no_op(torch_cuda):
     ro.close()
 
 
+@pytest.mark.parametrize("sizes", [(2, 3, 4, 5), (6, 7, 32, 33), (62, 63, 65, 100)])
+def test_grid_sizes(torch_cuda, sizes):
+    """Grids whose cells fill their bricks of 3 x 3 x 3, leave one or two over, or fit in one brick,
+    side by side in one scene; probes on both sides of every face of the box."""
+    sc = synth.make_scene("c2", num_envs=64, num_steps=3)
+    sc.noise = synth.NoiseParams(seed=sc.noise.seed)
+    sc.grids = [synth.make_objects(len(sc.grids), np.random.default_rng(5), n=sizes[i % 4])[i]
+                for i in range(len(sc.grids))]
+    inp = synth.make_inputs(sc)
+    inp.link_state[:, :3, ::3] *= np.float32(1.5)     # a third of the links: near, past and beyond the faces
+    ref = oracle_ref(sc, inp)
+    g = run_gpu(sc, inp)
+    parity.compare(g, ref, sc.layout.num_taxels, noisy=False, link_offset=sc.layout.link_offset)
+
+
 @pytest.mark.parametrize("counts, E, noise", [
     ([8] * 5 + [1, 7, 9], 65, "banded"),           # one env past a workgroup of 64; waves that end early
     ([64, 65, 130, 8], 17, "banded"),              # links on both sides of the store policy's bound
