@@ -4,8 +4,8 @@
 // launch for them: lane r <-> (env el = r / np, taxel k = r % np), np = n_l rounded up to a
 // multiple of 8, about 128..512 readouts per block whatever the link size (the plan's target), so
 // uneven links waste few lanes; the waves that a short link does not need end at once and leave their
-// slots to other blocks, whose memory latency and arithmetic overlap.  Because a block only ever sees one link, everything that couples taxels
-// stays inside the block:
+// slots to other blocks, whose memory latency and arithmetic overlap.  Because a block only ever sees
+// one link, everything that couples taxels stays inside the block:
 //   - dense crosstalk C_l Z_l runs on MFMA (16x16x32 BF16) with the six channels of all the
 //     block's envs as the N columns; the link's A fragments are staged in LDS for the launch
 //     (or read from L2 when they do not fit) and Z goes through an LDS staging area;
@@ -18,10 +18,10 @@
 //
 // Per step (four barriers): the loader lanes build the rotation matrices from the pose scalars
 // that were prefetched one or two per lane during the previous step; then the readout (probe point,
-// gathers from the bricked grid, depth, contact, force/torque, proximity), its non-temporal
-// stores (unit-stride runs of n_l floats per env), contact bits into LDS windows and the clean
-// group sums; then the clean epilogue (bit words, link sums) and the crosstalk MFMA; then the
-// noise chain and its outputs; then the noisy epilogue.
+// gathers from the bricked grid, depth, contact, force/torque, proximity), its stores (unit-stride
+// runs of n_l floats per env), contact bits into LDS windows and the clean group sums; then the clean
+// epilogue (bit words, link sums) and the crosstalk MFMA; then the noise chain and its outputs; then
+// the noisy epilogue.
 //
 // The physical block id is remapped so that each of the 8 XCDs works through a contiguous
 // range of items (neighbouring blocks share envs and their objects' bricks in that XCD's L2).

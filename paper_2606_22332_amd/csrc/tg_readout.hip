@@ -180,8 +180,6 @@ KernelFn select_kernel(int noise, int xt, int hy, int obj, int full) {
   return full ? select_kernel_f<1>(noise, xt, hy, obj) : select_kernel_f<0>(noise, xt, hy, obj);
 }
 
-// Work plan: envs per block for each link (about `target` readouts per block), the
-// (link, first env) items sorted by env, the LDS carve-up sized for the largest link.
 // Links of this many taxels and more write their outputs with non-temporal stores (LinkInfo::stream).
 // A link of 8 to 40 taxels writes runs of 32 to 160 bytes, so most cache lines are written by two to
 // four workgroups; non-temporal stores sent each part to memory by itself (48 M write requests of
@@ -202,6 +200,8 @@ constexpr int MAX_ENVS = 64;
 // of 4096 envs 51.6 us, 51.9, 54.6), and 256 for the shorter clean readout, whose workgroups
 // otherwise spend their time starting (2000 envs x 16 steps 188 us, 192 at 128, 199 at 512).
 int default_target(const tg_readout* h) { return h->xt == 2 ? 512 : (h->noise ? 128 : 256); }
+// Work plan: envs per block for each link (about `target` readouts per block), the
+// (link, first env) items sorted by env, the LDS carve-up sized for the largest link.
 tg_status plan_links(tg_readout* h, int target) {
   const int L = h->L, E = h->E;
   const int32_t* off = h->cfg.link_taxel_offset;
