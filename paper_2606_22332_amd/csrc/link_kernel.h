@@ -205,8 +205,8 @@ __global__ void __launch_bounds__(512, 4) tg_link_kernel(const KLaunch qarg) {
 #define li (*lip)
   const int n = li.n, envs = li.envs;
   const int tid = threadIdx.x;
-  // The threads this link needs; the waves past them end here (a barrier counts the waves that are
-  // left), so short links do not hold wave slots that the launch's longest link asked for.
+  // The threads that work on this link; the waves past them end here (a barrier counts the waves that
+  // are left), so short links do not hold wave slots that the launch's longest link asked for.
   const int nthr = li.nthr;
   if (tid >= nthr) return;
   LinkLds Ld;   // field by field: the source lives in the constant address space

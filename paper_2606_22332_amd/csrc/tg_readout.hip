@@ -195,7 +195,7 @@ constexpr int STREAM_MIN_TAXELS = 64;
 constexpr int MAX_ENVS = 64;
 // Readouts per workgroup of a new handle (the autotuner and set_work_plan change it).  Dense crosstalk
 // stages a link's matrix per workgroup, so large ones pay: 1024-taxel hand, 20480 envs x 16 steps
-// 14.5 ms at 512, 15.3 at 256, 17.3 at 128.  Without it a workgroup shares nothing but its barriers:
+// 14.5 ms at 512 (now 13.65), 15.3 at 256, 17.3 at 128.  Without it a workgroup shares nothing but its barriers:
 // with noise 128 (200-taxel hand, 1024 envs x 100 steps 0.98 ms, 1.04 at 256, 1.02 at 512; one step
 // of 4096 envs 51.6 us, 51.9, 54.6), and 256 for the shorter clean readout, whose workgroups
 // otherwise spend their time starting (2000 envs x 16 steps 188 us, 192 at 128, 199 at 512).
@@ -227,6 +227,11 @@ tg_status plan_links(tg_readout* h, int target) {
   }
   if (nthr > 512) return TG_ERR_UNSUPPORTED;
   h->threads = nthr;
+  // Dense crosstalk shares its tiles out over all waves of a workgroup, so there the waves past a
+  // link's own stay and take their part: 1024-taxel hand, 20480 envs, 64 steps 46.4 ms, 48.1 with
+  // those waves ended; 16 steps with every output 13.65 and 14.0 ms.
+  if (h->xt == 2)
+    for (int l = 0; l < L; ++l) h->links[l].nthr = nthr;
   // LDS layout: max over links of each region
   int64_t pose = 0, bits = 0, bt = 0, dt = 0, tax = 0, role = 0;
   for (int l = 0; l < L; ++l) {
