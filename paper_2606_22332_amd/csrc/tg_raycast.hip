@@ -25,13 +25,14 @@
 // The traversals park far children on a stack in LDS (one column per lane, so equal stack depths
 // fall in different banks).  They are of very unequal length (none to some dozens of nodes), so a lane
 // that ends one takes the next of the queue (walk below).
-// Bound: vector issue with part of the lanes at work, and the L1's data rate (62% busy): the nodes and
-// triangles come from L1 / L2, the meshes are a few hundred KB.  4096 envs x 200 probes x 16 steps, a
-// third of them in contact: 3.26 ms with a thread a probe, whose instructions had 10 of 64 lanes at
-// work; 2.42 ms with the reached probes packed and lanes refilled for the sphere query, 1.84 ms with
-// the ray query likewise and stacks of 4 bytes an entry (a key beside it, tested again before a
-// record is opened, cost 0.3 ms: its LDS holds fewer waves), 1.36 ms with each kind of step taken until no
-// lane waits for it (until fewer than 24 do: 1.76 ms) and spans of 3 chunks.
+// Bound: vector issue (all of the SIMDs' cycles at 100 steps) with 24 of 64 lanes at work, and behind it
+// the L1's data rate: the nodes and triangles come from L1 / L2, the meshes are a few hundred KB.
+// 4096 envs x 200 probes x 16 steps, a third of them in contact: 3.26 ms with a thread a probe, whose
+// instructions had 10 of 64 lanes at work; 2.42 ms with the reached probes packed and lanes refilled
+// for the sphere query, 1.84 ms with the ray query likewise and stacks of 4 bytes an entry (a key
+// beside it, tested again before a record is opened, cost 0.3 ms: its LDS holds fewer waves), 1.36 ms
+// with each kind of step taken until no lane waits for it (until fewer than 24 do: 1.76 ms) and spans
+// of 3 chunks.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
