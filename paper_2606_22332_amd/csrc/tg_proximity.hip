@@ -323,9 +323,10 @@ __global__ __launch_bounds__(PX_THREADS, 5) void tg_prox_kernel(const ProxParams
           for (int g = 0; g < ng; g += 8) {
             if (cnt > PX_LIST - 64) {
               run_list(cnt & ~7);
-              const int left = list[(cnt & ~7) + (lane & 7)];
+              const int done = cnt & ~7;   // (the list may be full: nothing is left past its end then)
+              cnt -= done;
+              const int left = lane < cnt ? list[done + lane] : 0;
               __builtin_amdgcn_wave_barrier();
-              cnt &= 7;
               if (lane < cnt) list[lane] = left;
             }
             const int gi = g + (lane >> 3);

@@ -212,3 +212,20 @@ def test_tile_edges(torch_cuda, counts, points, radius, scale, quat):
             check((g_ft / unit)[:, :, envs], g_m[:, envs] / scale, ((r_ft / unit)[:, :, envs], r_m[:, envs] / scale, cnt[:, envs]),
                   vs[:, envs], radius=radius, k_s=k_s, n_pts=max(n, 1))
     assert radius < 1e-3 or (r_m > 0).any()
+
+
+@pytest.mark.parametrize("points", [2048, 2056, 2560, 4096, 8192, 8193, 20000])
+def test_full_lists(torch_cuda, points):
+    """Clouds that lie inside every probe's sphere whole, so every chunk of 8 points is listed: the
+    lists of 256 chunks fill exactly (2048 points), are run through and go on; above 8192 points the
+    spheres over 64 groups are tested first (20000: three of them)."""
+    E, S, radius = 5, 2, 0.15
+    sc = synth.make_scene("c2", num_envs=E, num_steps=S)
+    sc.layout = synth.make_layout([20, 16, 5])
+    inp = synth.make_inputs(sc)
+    rng = np.random.default_rng(points)
+    clouds = [rng.uniform(-0.02, 0.02, (points, 3)).astype(np.float32) for _ in sc.grids]
+    g_ft, g_m = run_gpu(sc, clouds, inp, radius=radius)
+    ref = run_oracle(sc, clouds, inp, radius=radius)
+    assert np.all(ref[2] == points)
+    check(g_ft, g_m, ref, velocity_scale(inp, sc), radius=radius, n_pts=points)
