@@ -15,21 +15,22 @@
 // the list eight chunks at a time.  Every (point, probe) pair of a listed chunk is evaluated,
 // without branches, as two contractions on the matrix cores in FP32 (v_mfma_f32_4x4x1: 16
 // independent 4 x 4 blocks, the points broadcast to the blocks of the tile's probe quads):
-//   |p - q|^2 = |q|^2 - 2 p . q + |p|^2    with p and q taken from the tile's centre, and
-//   (S1 + S0 q, S0) = sum over points of max(R - |p - q|, 0) (p, 1).
-// Taking p and q from the tile's centre keeps the three terms of the square within a few R^2 (a
-// tile's probes lie within R of its centre), so the square is as exact as one of differences
-// (error of the channels against FP64 over 16 steps of the hand: 1.2e-7; 4.4e-7 with differences
-// summed in one chain per probe).
+//   p - q = p 1 + (-q), one axis at a time, and
+//   (S1 + S0 q, S0) = sum over points of max(R - |p - q|, 0) (p, 1), p and q from the tile's centre.
+// Each axis of a difference is rounded once, as a subtraction would be, so a pair's penetration has
+// the error of its own distance however near the point and however wide the tile; the square as
+// |q|^2 - 2 p . q + |p|^2, a quarter of the vector instructions, loses the digits of near points (a
+// point at a probe of R = 1 cm: 5 um off) and of small probes in wide tiles.  Error of the channels
+// against FP64 over 16 steps of the hand: 1.2e-7; 4.4e-7 with the sums in one chain per probe.
 //
-// Bound: vector issue (79% of the SIMDs' cycles): per 256 pairs 4 square roots, 4 subtractions and
-// the 8 MFMA, about 10 instructions of loading and centring the points, and as much again of
-// sphere tests and set-up per tile.  Measured on the hand, 4096 envs x 200 taxels x 16 steps,
-// 5000-point clouds: 4.1 ms against 21.4 ms for a thread per probe walking the rows of a cell
-// grid, where the lanes of a wave ran the union of their runs and a pair cost about 13 vector
-// instructions.  About 766 pairs are evaluated per probe (372 lie inside the sphere).  Chunks of 4
-// points and of 16 evaluate 704 and 856, but cost or save sphere tests: 4.5 ms with 4.  A sphere
-// instead of a box around the tile evaluates 986.
+// Bound: vector issue: per 256 pairs 12 instructions for the squares, 4 square roots, 4 subtractions
+// and the 7 MFMA, and about as much again of loads, sphere tests and set-up per tile.  Measured on the
+// hand, 4096 envs x 200 taxels x 16 steps, 5000-point clouds: 4.7 ms (4.1 with the expanded square)
+// against 21.4 ms for a thread per probe walking the rows of a cell grid, where the lanes of a wave ran
+// the union of their runs and a pair cost about 13 vector instructions.  About 766 pairs are evaluated
+// per probe (372 lie inside the sphere).  Before the differences: chunks of 4 points and of 16 evaluate
+// 704 and 856, but cost or save sphere tests: 4.5 ms with 4; a sphere instead of a box around the tile
+// evaluates 986.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -114,37 +115,33 @@ __device__ __forceinline__ float clamp01(float x) { return __builtin_amdgcn_fmed
 // Eight listed chunks against the 4 << NQ probes of a tile.  Lane 4 i + k carries point k of quad i
 // and row k of quad i's moment operand (x: one value per point).  Block b of the 16 serves probe
 // quad b mod 2^NQ; the blocks that differ only in it form a broadcast group, which takes each of
-// its own point quads in turn (the instruction's broadcast-block field).  The chains of the turns
-// are interleaved, so no instruction waits on the one before it.
+// its own point quads in turn (the instruction's broadcast-block field).  qx, qy, qz: the lane's
+// probe, negated, once for each of a quad's points, so that p 1 - q comes out of the matrix core as
+// one rounded difference.
 template <int NQ>
-__device__ __forceinline__ void prox_group(const float4& pt, const f32x4& x, float qx, float qy, float qz, float qq,
-                                           float R, f32x4& M0, f32x4& M1) {
-  const float pp = fmaf(pt.z, pt.z, fmaf(pt.y, pt.y, pt.x * pt.x));
-  f32x4 d[4];
+__device__ __forceinline__ void prox_group(const float4& pt, const f32x4& x, const f32x4& qx, const f32x4& qy,
+                                           const f32x4& qz, float R, f32x4& M0, f32x4& M1) {
+  f32x4 w[4];
 #define PX_TURNS(F) F(0) F(1) F(2) F(3)
 #define PX_ON(A) if constexpr ((A) < (1 << NQ))
-#define PX_X(A) PX_ON(A) d[A] = __builtin_amdgcn_mfma_f32_4x4x1f32(pt.x, qx, f32x4{qq, qq, qq, qq}, NQ, A, 0);
-#define PX_Y(A) PX_ON(A) d[A] = __builtin_amdgcn_mfma_f32_4x4x1f32(pt.y, qy, d[A], NQ, A, 0);
-#define PX_Z(A) PX_ON(A) d[A] = __builtin_amdgcn_mfma_f32_4x4x1f32(pt.z, qz, d[A], NQ, A, 0);
-#define PX_P(A) PX_ON(A) d[A] = __builtin_amdgcn_mfma_f32_4x4x1f32(pp, 1.0f, d[A], NQ, A, 0);
 #define PX_W(A)                                                                                                 \
-  PX_ON(A) _Pragma("unroll") for (int r = 0; r < 4; ++r)                                                        \
-      d[A][r] = clamp01(R - __builtin_amdgcn_sqrtf(fabsf(d[A][r])));
+  PX_ON(A) {                                                                                                    \
+    const f32x4 dx = __builtin_amdgcn_mfma_f32_4x4x1f32(pt.x, 1.0f, qx, NQ, A, 0);                              \
+    const f32x4 dy = __builtin_amdgcn_mfma_f32_4x4x1f32(pt.y, 1.0f, qy, NQ, A, 0);                              \
+    const f32x4 dz = __builtin_amdgcn_mfma_f32_4x4x1f32(pt.z, 1.0f, qz, NQ, A, 0);                              \
+    _Pragma("unroll") for (int r = 0; r < 4; ++r)                                                               \
+        w[A][r] = clamp01(R - __builtin_amdgcn_sqrtf(fmaf(dz[r], dz[r], fmaf(dy[r], dy[r], dx[r] * dx[r]))));   \
+  }
 #define PX_M(A)                                                                                                 \
   PX_ON(A) {                                                                                                    \
-    M0 = __builtin_amdgcn_mfma_f32_4x4x1f32(x[0], d[A][0], M0, NQ, A, 0);                                       \
-    M1 = __builtin_amdgcn_mfma_f32_4x4x1f32(x[1], d[A][1], M1, NQ, A, 0);                                       \
-    M0 = __builtin_amdgcn_mfma_f32_4x4x1f32(x[2], d[A][2], M0, NQ, A, 0);                                       \
-    M1 = __builtin_amdgcn_mfma_f32_4x4x1f32(x[3], d[A][3], M1, NQ, A, 0);                                       \
+    M0 = __builtin_amdgcn_mfma_f32_4x4x1f32(x[0], w[A][0], M0, NQ, A, 0);                                       \
+    M1 = __builtin_amdgcn_mfma_f32_4x4x1f32(x[1], w[A][1], M1, NQ, A, 0);                                       \
+    M0 = __builtin_amdgcn_mfma_f32_4x4x1f32(x[2], w[A][2], M0, NQ, A, 0);                                       \
+    M1 = __builtin_amdgcn_mfma_f32_4x4x1f32(x[3], w[A][3], M1, NQ, A, 0);                                       \
   }
-  PX_TURNS(PX_X) PX_TURNS(PX_Y) PX_TURNS(PX_Z) PX_TURNS(PX_P)
   PX_TURNS(PX_W) PX_TURNS(PX_M)
 #undef PX_TURNS
 #undef PX_ON
-#undef PX_X
-#undef PX_Y
-#undef PX_Z
-#undef PX_P
 #undef PX_W
 #undef PX_M
 }
@@ -185,7 +182,8 @@ __device__ __forceinline__ void load_pose13(const float* state, int64_t cols, in
 }
 }  // namespace
 
-__global__ __launch_bounds__(PX_THREADS, 5) void tg_prox_kernel(const ProxParams p, const ProxLaunch q) {
+// 4 waves a SIMD: 127 registers and no scratch, 4.69 ms; 5 waves spill 27 of 96 registers: 4.74.
+__global__ __launch_bounds__(PX_THREADS, 4) void tg_prox_kernel(const ProxParams p, const ProxLaunch q) {
   __shared__ float4 s_q[2 * PX_THREADS];      // per env: the span's probe centres (and R), its tile centres
   __shared__ float4 s_rot[PX_THREADS];        // per (env, tile): rotation link frame -> object frame
   __shared__ float4 s_sum[PX_THREADS];        // per (env, probe): S0, S1 (object frame)
@@ -262,7 +260,6 @@ __global__ __launch_bounds__(PX_THREADS, 5) void tg_prox_kernel(const ProxParams
       const float4 pr = pi >= 0 ? s_q[el * per + pi] : make_float4(ctr.x, ctr.y, ctr.z, 0.f);
       const float R = pr.w;
       const float ax = pr.x - ctr.x, ay = pr.y - ctr.y, az = pr.z - ctr.z;
-      const float qq = fmaf(az, az, fmaf(ay, ay, ax * ax));
       f32x4 M = {0.f, 0.f, 0.f, 0.f};
       if (oid >= 0) {
         // The tile's box in its link's frame, and how far its probes sense: grown by a relative 1e-5
@@ -287,7 +284,8 @@ __global__ __launch_bounds__(PX_THREADS, 5) void tg_prox_kernel(const ProxParams
           const float r = c.w + far;
           return !(fmaf(z[2], z[2], fmaf(z[1], z[1], z[0] * z[0])) >= r * r);
         };
-        const float bx = -2.0f * ax, by = -2.0f * ay, bz = -2.0f * az;
+        const f32x4 qx = {-pr.x, -pr.x, -pr.x, -pr.x}, qy = {-pr.y, -pr.y, -pr.y, -pr.y},
+                    qz = {-pr.z, -pr.z, -pr.z, -pr.z};
         const float cc = col == 0 ? ctr.x : (col == 1 ? ctr.y : (col == 2 ? ctr.z : 0.f));
         const CloudDesc cd = p.clouds[oid];
         f32x4 M1 = {0.f, 0.f, 0.f, 0.f};
@@ -296,11 +294,10 @@ __global__ __launch_bounds__(PX_THREADS, 5) void tg_prox_kernel(const ProxParams
           for (int it = 0; it < n; it += 8) {
             const int i = it + (lane >> 3);
             const int64_t at = (int64_t)(i < n ? list[i] : p.dummy) * PX_CHUNK + (lane & 7);
-            float4 pt = p.pts[at];
+            const float4 pt = p.pts[at];
             const float4 m = p.mom[at];
-            pt.x -= ctr.x; pt.y -= ctr.y; pt.z -= ctr.z;
             const f32x4 x = {m.x - cc, m.y - cc, m.z - cc, m.w - cc};
-            prox_group<decltype(nqc)::value>(pt, x, bx, by, bz, qq, R, M, M1);
+            prox_group<decltype(nqc)::value>(pt, x, qx, qy, qz, R, M, M1);
           }
         };
         int cnt = 0;

@@ -229,3 +229,44 @@ def test_full_lists(torch_cuda, points):
     ref = run_oracle(sc, clouds, inp, radius=radius)
     assert np.all(ref[2] == points)
     check(g_ft, g_m, ref, velocity_scale(inp, sc), radius=radius, n_pts=points)
+
+
+def identity_scene(counts, radii, offsets, seed):
+    """Links and objects at the origin, so the GPU's probe centres are the taxels' positions without
+    rounding; each object's cloud holds one point for every taxel, at one of `offsets` from it."""
+    sc = synth.make_scene("c2", num_envs=len(offsets), num_steps=1)
+    sc.layout = synth.make_layout(counts)
+    inp = synth.make_inputs(sc)
+    inp.link_state[:] = 0
+    inp.link_state[:, 3] = 1
+    inp.obj_state = None
+    sc.grids = sc.grids[:1] * len(offsets)
+    inp.obj_id[:] = np.arange(len(offsets))
+    rng = np.random.default_rng(seed)
+    T = sc.layout.num_taxels
+    clouds = []
+    for o in offsets:
+        d = rng.normal(size=(T, 3))
+        clouds.append((sc.layout.pos + o * d / np.linalg.norm(d, axis=1, keepdims=True)).astype(np.float32))
+    return sc, inp, clouds, np.resize(np.asarray(radii, np.float32), T)
+
+
+@pytest.mark.parametrize("radii", [[0.01], [0.001, 0.01], [0.02, 0.002, 0.05, 0.001]])
+def test_points_at_the_probes(torch_cuda, radii):
+    """Points at a probe's centre and at 1 um to 0.5 mm from it, one radius or several on a link.  A
+    point's penetration is R - |p - q| in FP32: three rounded differences, their squares' sum, the
+    hardware square root (1 ulp) and the last difference, less than 8 x 2^-24 R, and a sum of n
+    terms rounds by n x 2^-24 of its value."""
+    sc, inp, clouds, rad = identity_scene([24, 7], radii, [0.0, 1e-6, 1e-5, 1e-4, 5e-4], 11)
+    _, g_m = run_gpu(sc, clouds, inp, radius=rad)
+    _, r_m, cnt = run_oracle_radii(sc, clouds, inp, rad)
+    tol = 2.0 ** -24 * cnt * (8 * rad + r_m)
+    err = np.abs(g_m - r_m)
+    print(dict(ratio=float((err / np.maximum(tol, 1e-30)).max()), points=float(cnt.mean())))
+    assert np.all(r_m > 0) and np.all(err <= tol)
+
+
+def run_oracle_radii(sc, clouds, inp, radii, **kw):
+    lay = sc.layout
+    return oracle.prox_run(lay.link_offset, lay.pos, lay.normal, radii, clouds, inp.link_state, inp.obj_id,
+                           inp.obj_state, inp.step0, with_count=True, **kw)
