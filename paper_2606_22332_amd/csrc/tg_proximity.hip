@@ -508,17 +508,28 @@ float4 bounding_sphere(const CloudPoint* p, int64_t n, float unit) {
                      (float)((std::sqrt(r2) * (1.0 + 1e-6) + 1e-6 * size) * (double)unit));
 }
 
-// Split taxels idx[b, e) of one link into tiles of at most 16 probes that lie within `reach` of
-// their tile's centre.
-void split_tiles(const float* pos, int32_t* idx, int b, int e, int link, int j0, float reach,
+// Split taxels idx[b, e) of one link into tiles of at most 16 probes, their sensing radii within a
+// factor of two and none further from the tile's centre than the smallest of them: the moments are
+// taken from the centre, so a wider tile would cost its small probes digits of their torque.
+void split_tiles(const float* pos, const float* radius, int32_t* idx, int b, int e, int link, int j0,
                  std::vector<ProxTile>& out) {
-  float lo[3], hi[3];
+  float lo[3], hi[3], rlo = INFINITY, rhi = 0.f;   // (a radius of 0 senses nothing, wherever it lies)
   for (int k = 0; k < 3; ++k) lo[k] = hi[k] = pos[3 * idx[b] + k];
-  for (int i = b; i < e; ++i)
+  for (int i = b; i < e; ++i) {
     for (int k = 0; k < 3; ++k) {
       lo[k] = std::min(lo[k], pos[3 * idx[i] + k]);
       hi[k] = std::max(hi[k], pos[3 * idx[i] + k]);
     }
+    rhi = std::max(rhi, radius[idx[i]]);
+    if (radius[idx[i]] > 0.f) rlo = std::min(rlo, radius[idx[i]]);
+  }
+  if (rhi > 2.0 * rlo) {
+    const double at = std::sqrt((double)rlo * rhi);
+    const int left = (int)(std::stable_partition(idx + b, idx + e, [&](int32_t j) { return radius[j] < at; }) - idx);
+    split_tiles(pos, radius, idx, b, left, link, j0, out);
+    split_tiles(pos, radius, idx, left, e, link, j0, out);
+    return;
+  }
   ProxTile t{};
   float r2 = 0.f;
   int ax = 0;
@@ -532,7 +543,7 @@ void split_tiles(const float* pos, int32_t* idx, int b, int e, int link, int j0,
     r2 = std::max(r2, d2);
   }
   const int n = e - b;
-  if (n == 1 || (n <= 16 && r2 <= reach * reach)) {
+  if (n == 1 || (n <= 16 && r2 <= (double)rlo * rlo)) {
     t.link = link;
     t.nq = n > 8 ? 2 : (n > 4 ? 1 : 0);
     for (int i = 0; i < 16; ++i) t.probe[i] = (int16_t)(i < n ? idx[b + i] - j0 : -1);
@@ -543,8 +554,8 @@ void split_tiles(const float* pos, int32_t* idx, int b, int e, int link, int j0,
   std::nth_element(idx + b, idx + b + left, idx + e, [&](int32_t u, int32_t w) {
     return pos[3 * u + ax] < pos[3 * w + ax] || (pos[3 * u + ax] == pos[3 * w + ax] && u < w);
   });
-  split_tiles(pos, idx, b, b + left, link, j0, reach, out);
-  split_tiles(pos, idx, b + left, e, link, j0, reach, out);
+  split_tiles(pos, radius, idx, b, b + left, link, j0, out);
+  split_tiles(pos, radius, idx, b + left, e, link, j0, out);
 }
 }  // namespace
 
@@ -579,8 +590,7 @@ tg_status tg_prox_create(const tg_prox_config* cfg, tg_prox** out) {
       std::memcpy(&lf, &li, 4);
       tb[j] = make_float4(cfg->taxel_normal[3 * j], cfg->taxel_normal[3 * j + 1], cfg->taxel_normal[3 * j + 2], lf);
     }
-  // Spans of at most PX_THREADS taxels and their tiles, the largest first.  A tile's probes lie
-  // within the largest sensing radius of its centre (see the head of this file).
+  // Spans of at most PX_THREADS taxels and their tiles, the largest first.
   std::vector<ProxSpan> spans;
   std::vector<ProxTile> tiles;
   std::vector<int32_t> order(T);
@@ -589,7 +599,7 @@ tg_status tg_prox_create(const tg_prox_config* cfg, tg_prox** out) {
     const int j1 = std::min(T, j0 + PX_THREADS), t0 = (int)tiles.size();
     for (int l = 0; l < L; ++l) {
       const int b = std::max(off[l], j0), e = std::min(off[l + 1], j1);
-      if (b < e) split_tiles(cfg->taxel_pos, order.data(), b, e, l, j0, rmax, tiles);
+      if (b < e) split_tiles(cfg->taxel_pos, cfg->sensing_radius, order.data(), b, e, l, j0, tiles);
     }
     std::stable_sort(tiles.begin() + t0, tiles.end(), [](const ProxTile& u, const ProxTile& w) { return u.nq > w.nq; });
     spans.push_back({j0, j1 - j0, t0, (int)tiles.size() - t0});

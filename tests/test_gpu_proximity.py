@@ -266,6 +266,30 @@ def test_points_at_the_probes(torch_cuda, radii):
     assert np.all(r_m > 0) and np.all(err <= tol)
 
 
+def test_mixed_radii_in_wide_layouts(torch_cuda):
+    """Probes of 1 mm and of 0.5 m in turn, 6 cm from one to the next: the torque of the
+    small ones keeps its digits.  In a moment sum P (p - q) of n points each term is off by its P's
+    error (8 x 2^-24 R, see above) times R, and the sum, formed about a point within R of q, by
+    (n + 2) x 2^-24 of sum P times 3 R; twice that for a component of its cross product with a normal."""
+    sc, inp, clouds, rad = identity_scene([24, 7], [0.001, 0.5], [0.0, 1e-5, 1e-4, 5e-4, 7e-4], 12)
+    grow = lambda a: np.ascontiguousarray(a * np.float32(32), np.float32)
+    clouds = [grow(sc.layout.pos) + (c - sc.layout.pos) for c in clouds]
+    clouds = [c.astype(np.float32) for c in clouds]
+    sc.layout.pos = grow(sc.layout.pos)
+    g_ft, g_m = run_gpu(sc, clouds, inp, radius=rad)
+    r_ft, r_m, cnt = run_oracle_radii(sc, clouds, inp, rad)
+    u = 2.0 ** -24
+    m_tol = u * cnt * (8 * rad + r_m)
+    krho = 300.0 * 100.0 / len(clouds[0])
+    t_tol = krho * 2 * u * (8 * cnt * rad * rad + (cnt + 2) * 3 * rad * r_m)
+    m_err, t_err = np.abs(g_m - r_m), np.abs(g_ft[:, 3:] - r_ft[:, 3:]).max(1)
+    small = rad < 0.01
+    print(dict(m=float((m_err / m_tol).max()), t=float((t_err / t_tol).max()),
+               t_small=float((t_err / t_tol)[..., small].max())))
+    assert np.all(r_m > 0)
+    assert np.all(m_err <= m_tol) and np.all(t_err <= t_tol)
+
+
 def run_oracle_radii(sc, clouds, inp, radii, **kw):
     lay = sc.layout
     return oracle.prox_run(lay.link_offset, lay.pos, lay.normal, radii, clouds, inp.link_state, inp.obj_id,
