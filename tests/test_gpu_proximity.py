@@ -290,6 +290,24 @@ def test_mixed_radii_in_wide_layouts(torch_cuda):
     assert np.all(m_err <= m_tol) and np.all(t_err <= t_tol)
 
 
+@pytest.mark.parametrize("odd", [2.0, 1e25, np.inf])
+def test_one_huge_radius_leaves_the_others(torch_cuda, odd):
+    """One taxel with a radius of 2 m, 1e25 m or infinity (which senses nothing) on a hand of 1 cm."""
+    sc, inp, clouds = scene(6, 2)
+    lay = sc.layout
+    rad = np.full(lay.num_taxels, 0.01, np.float32)
+    rad[47] = odd
+    others = rad != np.float32(odd)
+    g_ft, g_m = run_gpu(sc, clouds, inp, radius=rad)
+    r_ft, r_m, cnt = run_oracle_radii(sc, clouds, inp, np.where(others, rad, np.float32(0.01)))
+    check(g_ft[..., others], g_m[..., others], (r_ft[..., others], r_m[..., others], cnt[..., others]),
+          velocity_scale(inp, sc)[..., others])
+    if np.isinf(odd):
+        assert np.all(g_m[..., 47] == 0) and np.all(g_ft[..., 47] == 0)
+    else:   # every point lies inside: 5000 penetrations within 0.2 m of the radius, summed in FP32
+        assert np.all(np.abs(g_m[..., 47] / (5000.0 * np.float64(rad[47])) - 1) <= 0.2 / odd + 5000 * 2.0 ** -24)
+
+
 def run_oracle_radii(sc, clouds, inp, radii, **kw):
     lay = sc.layout
     return oracle.prox_run(lay.link_offset, lay.pos, lay.normal, radii, clouds, inp.link_state, inp.obj_id,
