@@ -535,7 +535,7 @@ void split_tiles(const float* pos, const float* radius, int32_t* idx, int b, int
   float r2 = 0.f;
   int ax = 0;
   for (int k = 0; k < 3; ++k) {
-    t.centre[k] = 0.5f * (lo[k] + hi[k]);
+    t.centre[k] = 0.5f * lo[k] + 0.5f * hi[k];
     if (hi[k] - lo[k] > hi[ax] - lo[ax]) ax = k;
   }
   for (int i = b; i < e; ++i) {
@@ -600,7 +600,14 @@ tg_status tg_prox_create(const tg_prox_config* cfg, tg_prox** out) {
     const int j1 = std::min(T, j0 + PX_THREADS), t0 = (int)tiles.size();
     for (int l = 0; l < L; ++l) {
       const int b = std::max(off[l], j0), e = std::min(off[l + 1], j1);
-      if (b < e) split_tiles(cfg->taxel_pos, cfg->sensing_radius, order.data(), b, e, l, j0, tiles);
+      // a taxel without a finite position senses nothing; in a tile of its own it spoils no other's centre
+      const auto placed = [&](int32_t j) {
+        return std::isfinite(ta[j].x) && std::isfinite(ta[j].y) && std::isfinite(ta[j].z);
+      };
+      int f = b;
+      if (b < e) f = (int)(std::stable_partition(order.begin() + b, order.begin() + e, placed) - order.begin());
+      if (b < f) split_tiles(cfg->taxel_pos, cfg->sensing_radius, order.data(), b, f, l, j0, tiles);
+      for (; f < e; ++f) split_tiles(cfg->taxel_pos, cfg->sensing_radius, order.data(), f, f + 1, l, j0, tiles);
     }
     std::stable_sort(tiles.begin() + t0, tiles.end(), [](const ProxTile& u, const ProxTile& w) { return u.nq > w.nq; });
     spans.push_back({j0, j1 - j0, t0, (int)tiles.size() - t0});

@@ -308,6 +308,23 @@ def test_one_huge_radius_leaves_the_others(torch_cuda, odd):
         assert np.all(np.abs(g_m[..., 47] / (5000.0 * np.float64(rad[47])) - 1) <= 0.2 / odd + 5000 * 2.0 ** -24)
 
 
+@pytest.mark.parametrize("odd", [np.nan, np.inf, 3e38])
+@pytest.mark.parametrize("taxel", [0, 40, 47])
+def test_one_taxel_without_a_place_leaves_the_others(torch_cuda, taxel, odd):
+    """A taxel with no finite position (first, last or inside its link), or out of the world: its
+    neighbours read what they read without it, itself nothing."""
+    sc, inp, clouds = scene(6, 2)
+    lay = sc.layout
+    pos = lay.pos.copy()
+    ref = run_oracle(sc, clouds, inp)
+    lay.pos = pos.copy()
+    lay.pos[taxel] = odd
+    others = np.arange(lay.num_taxels) != taxel
+    g_ft, g_m = run_gpu(sc, clouds, inp)
+    check(g_ft[..., others], g_m[..., others], tuple(a[..., others] for a in ref), velocity_scale(inp, sc)[..., others])
+    assert np.all(g_m[..., taxel] == 0)
+
+
 def run_oracle_radii(sc, clouds, inp, radii, **kw):
     lay = sc.layout
     return oracle.prox_run(lay.link_offset, lay.pos, lay.normal, radii, clouds, inp.link_state, inp.obj_id,
