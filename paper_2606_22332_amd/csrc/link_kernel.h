@@ -117,7 +117,9 @@ __device__ __forceinline__ void put_group_sums(float* P, int stride, const float
 // Per-link observations of one step (App. B.2: summed force and torque, contact count, agg_bool,
 // agg_force) from the group partials: one lane per (channel, env) item adds the env's groups in
 // order; output [11][L][E], items env-fastest so neighbouring lanes store neighbouring floats.
-// role: the items' (channel, env) in bytes.
+// role: the items' (channel, env) in bytes.  A long link's one lane per item adds up to 64 groups while
+// the block waits, so eight are read before they are added (read one at a time: links of 500 taxels,
+// 4096 envs x 16 steps 3.87 ms, of 200 taxels 2.84 ms; 2.93 and 2.49 so).
 template <class KP, class LI>
 __device__ __forceinline__ void link_reduce(KP& p, LI& li, const float* P, int stride, int e0, int l,
                                             float* out, const uint16_t* role) {
@@ -130,7 +132,17 @@ __device__ __forceinline__ void link_reduce(KP& p, LI& li, const float* P, int s
     if (e >= p.E) continue;
     const float* v = P + ch * stride + el * gpe;
     float acc = 0.f;
-    for (int g = 0; g < gpe; ++g) acc += v[g];
+    int g = 0;
+#pragma nounroll
+    for (; g + 8 <= gpe; g += 8) {
+      float t[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) t[i] = v[g + i];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) acc += t[i];
+    }
+#pragma nounroll
+    for (; g < gpe; ++g) acc += v[g];
     // byte offsets from the step's base: 11 * E * L * 4 fits 32 bits (checked at create)
     const uint32_t col = (uint32_t)l * (uint32_t)p.E + (uint32_t)e;
     const uint32_t el4 = (uint32_t)EL * 4u;

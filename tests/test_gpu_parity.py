@@ -509,3 +509,11 @@ def test_plans_agree(torch_cuda, counts, E, noise):
     for other in res[1:]:
         for k, v in res[0].items():
             assert np.array_equal(v, other[k]), k
+
+
+@pytest.mark.parametrize("counts, E, noise", [
+    ([56, 57, 64, 72, 500], 3, "off"),             # link sums of 7, 8, 8, 9 and 63 groups of 8 lanes
+])
+def test_plans_agree_on_more_hands(torch_cuda, counts, E, noise):
+    """As test_plans_agree."""
+    test_plans_agree(torch_cuda, counts, E, noise)
