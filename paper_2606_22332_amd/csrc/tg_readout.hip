@@ -180,15 +180,17 @@ KernelFn select_kernel(int noise, int xt, int hy, int obj, int full) {
   return full ? select_kernel_f<1>(noise, xt, hy, obj) : select_kernel_f<0>(noise, xt, hy, obj);
 }
 
-// Links of this many taxels and more write their outputs with non-temporal stores (LinkInfo::stream).
-// A link of 8 to 40 taxels writes runs of 32 to 160 bytes, so most cache lines are written by two to
-// four workgroups; non-temporal stores sent each part to memory by itself (48 M write requests of
-// 30 bytes per 100 steps of 1024 envs on the 200-taxel hand).  Rollout of that, its thermal step
-// included: 3.13 ms all non-temporal, 2.28 all plain; one step of 4096 envs 78 against 61 us.  On the
-// 1024-taxel hand (links of 25 to 128 taxels, 20480 envs x 16 steps) the line lies in between:
-// 15.87 ms all non-temporal, 15.20 / 14.87 / 14.73 / 14.79 / 14.98 with this bound at 33 / 48 / 64 /
-// 90 / 100, 16.1 all plain; plain stores for the shared lines of a run alone 15.07.
-constexpr int STREAM_MIN_TAXELS = 64;
+// Whether a link writes its outputs with non-temporal stores (LinkInfo::stream): where its runs of n
+// floats are whole 64-byte pieces of memory, or long enough that most of their pieces are.  A piece that
+// two workgroups share goes to memory twice unless L2 puts it together (48 M write requests of 30 bytes
+// per 100 steps of 1024 envs on the 200-taxel hand); whole ones only take L2's room from the grids.
+// Hands of 12 to 32 equal links, 4096 envs x 16 steps, all stores plain / non-temporal, in us:
+//   runs of whole pieces: links of 16 taxels 751 / 577, 32 1177 / 1059, 48 2231 / 2025, 64 2205 / 1974;
+//   others: 8 909 / 1919, 24 1052 / 1745, 40 1764 / 2144, 56 2477 / 2670, 60 2465 / 2817, 72 2849 / 2751.
+// On the 1024-taxel hand (links of 25 to 128 taxels, 20480 envs x 16 steps, dense crosstalk), with the
+// bound at 33 / 48 / 64 / 90 / 100 taxels, 15.20 / 14.87 / 14.73 / 14.79 / 14.98 ms; 15.87 all
+// non-temporal, 16.1 all plain.
+bool stream_stores(int off, int n, int T) { return n >= 64 || (off % 16 == 0 && n % 16 == 0 && T % 16 == 0); }
 // Most envs of a workgroup: 8-taxel links then fill 512 lanes.  (36, one prefetched scalar a lane,
 // and idle waves kept: 200-taxel hand, 1021 envs x 33 steps 595 us against 385, one step of 4096
 // envs 62 against 58.)
@@ -216,7 +218,7 @@ tg_status plan_links(tg_readout* h, int target) {
     li.envs = std::max(1, std::min(std::min(E, MAX_ENVS), target / li.np));
     li.nwin = li.n > 0 ? ((li.off + li.n - 1) >> 6) - (li.off >> 6) + 1 : 1;
     li.nt = (6 * li.envs + 15) / 16;
-    li.stream = li.n >= STREAM_MIN_TAXELS;
+    li.stream = stream_stores(li.off, li.n, h->T);
     const int n16 = ((li.n + 15) / 16) * 16, n32 = ((li.n + 31) / 32) * 32;
     li.kp = n32 + 8;    // B staging column stride (bf16): K tiles of 32, 16-byte aligned columns
     li.kpd = n16 + 4;   // result staging row stride (floats)

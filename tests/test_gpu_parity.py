@@ -513,6 +513,8 @@ def test_plans_agree(torch_cuda, counts, E, noise):
 
 @pytest.mark.parametrize("counts, E, noise", [
     ([56, 57, 64, 72, 500], 3, "off"),             # link sums of 7, 8, 8, 9 and 63 groups of 8 lanes
+    ([16, 48, 32, 16], 19, "banded"),              # runs of whole 64-byte pieces (T = 112)
+    ([16, 32, 8, 48, 63], 19, "banded"),           # some runs begin so, in planes that do not (T = 167)
 ])
 def test_plans_agree_on_more_hands(torch_cuda, counts, E, noise):
     """As test_plans_agree."""
