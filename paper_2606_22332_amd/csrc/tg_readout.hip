@@ -195,6 +195,11 @@ bool stream_stores(int off, int n, int T) { return n >= 64 || (off % 16 == 0 && 
 // and idle waves kept: 200-taxel hand, 1021 envs x 33 steps 595 us against 385, one step of 4096
 // envs 62 against 58.)
 constexpr int MAX_ENVS = 64;
+// Under dense crosstalk, whose staging areas grow with the envs: two workgroups a CU and the matrix's
+// fragments still fit its LDS then (62 KB each on the 200-taxel hand; 99 KB at 64 envs).  4096 envs x 16
+// steps at 64 / 36 envs: the 200-taxel hand 926 / 701 us, with moving objects 1078 / 804, one step 87 /
+// 66; one link of 512 taxels beside three of 40, 8 and 8, 2048 envs: 2187 / 1361.
+constexpr int MAX_ENVS_DENSE = 36;
 // Readouts per workgroup of a new handle (the autotuner and set_work_plan change it).  Dense crosstalk
 // stages a link's matrix per workgroup, so large ones pay: 1024-taxel hand, 20480 envs x 16 steps
 // 14.5 ms at 512 (now 13.65), 15.3 at 256, 17.3 at 128.  Without it a workgroup shares nothing but its barriers:
@@ -207,6 +212,7 @@ int default_target(const tg_readout* h) { return h->xt == 2 ? 512 : (h->noise ? 
 tg_status plan_links(tg_readout* h, int target) {
   const int L = h->L, E = h->E;
   const int32_t* off = h->cfg.link_taxel_offset;
+  const int max_envs = h->xt == 2 ? MAX_ENVS_DENSE : MAX_ENVS;
   int nthr = 64;
   for (int l = 0; l < L; ++l) {
     LinkInfo& li = h->links[l];
@@ -215,7 +221,7 @@ tg_status plan_links(tg_readout* h, int target) {
     if (li.n > 512) return TG_ERR_UNSUPPORTED;
     // envs per block: ~target readouts
     li.np = li.n > 0 ? (li.n + 7) & ~7 : 8;   // lanes per env: whole 8-lane groups
-    li.envs = std::max(1, std::min(std::min(E, MAX_ENVS), target / li.np));
+    li.envs = std::max(1, std::min(std::min(E, max_envs), target / li.np));
     li.nwin = li.n > 0 ? ((li.off + li.n - 1) >> 6) - (li.off >> 6) + 1 : 1;
     li.nt = (6 * li.envs + 15) / 16;
     li.stream = stream_stores(li.off, li.n, h->T);

@@ -514,6 +514,8 @@ def test_plans_agree(torch_cuda, counts, E, noise):
 @pytest.mark.parametrize("counts, E, noise", [
     ([56, 57, 64, 72, 500], 3, "off"),             # link sums of 7, 8, 8, 9 and 63 groups of 8 lanes
     ([16, 48, 32, 16], 19, "banded"),              # runs of whole 64-byte pieces (T = 112)
+    (synth.C2_LINKS, 70, "dense"),                 # links short enough for the most envs of a dense plan
+    ([512, 40, 8, 8], 37, "dense"),                # the same beside a link whose matrix does not fit in LDS
     ([16, 32, 8, 48, 63], 19, "banded"),           # some runs begin so, in planes that do not (T = 167)
 ])
 def test_plans_agree_on_more_hands(torch_cuda, counts, E, noise):
