@@ -235,10 +235,12 @@ tg_status plan_links(tg_readout* h, int target) {
   }
   if (nthr > 512) return TG_ERR_UNSUPPORTED;
   h->threads = nthr;
-  // Dense crosstalk shares its tiles out over all waves of a workgroup, so there the waves past a
-  // link's own stay and take their part: 1024-taxel hand, 20480 envs, 64 steps 46.4 ms, 48.1 with
-  // those waves ended; 16 steps with every output 13.65 and 14.0 ms.
-  if (h->xt == 2)
+  // With noise the waves past a link's own stay for the launch: they take their part of the dense
+  // crosstalk's tiles (1024-taxel hand, 20480 envs, 64 steps 46.4 ms, 48.1 with those waves ended; 16
+  // steps with every output 13.65 and 14.0 ms) and of the prefetch and the link sums (links of 500, 300,
+  // 200 and 24 taxels, banded crosstalk, 4096 envs x 16 steps 2.58 ms, 2.84 with them ended).  The clean
+  // readout is shorter and gains from the slots they leave (the same links 1.32 ms, 1.48 with them kept).
+  if (h->noise)
     for (int l = 0; l < L; ++l) h->links[l].nthr = nthr;
   // LDS layout: max over links of each region
   int64_t pose = 0, bits = 0, bt = 0, dt = 0, tax = 0, role = 0;

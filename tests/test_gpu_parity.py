@@ -516,6 +516,8 @@ def test_plans_agree(torch_cuda, counts, E, noise):
     ([16, 48, 32, 16], 19, "banded"),              # runs of whole 64-byte pieces (T = 112)
     (synth.C2_LINKS, 70, "dense"),                 # links short enough for the most envs of a dense plan
     ([512, 40, 8, 8], 37, "dense"),                # the same beside a link whose matrix does not fit in LDS
+    ([500, 300, 200, 24], 5, "banded"),            # links that need fewer waves than the launch has, with noise
+    ([500, 300, 200, 24], 5, "off"),               # and without
     ([16, 32, 8, 48, 63], 19, "banded"),           # some runs begin so, in planes that do not (T = 167)
 ])
 def test_plans_agree_on_more_hands(torch_cuda, counts, E, noise):
