@@ -202,11 +202,23 @@ constexpr int MAX_ENVS = 64;
 constexpr int MAX_ENVS_DENSE = 36;
 // Readouts per workgroup of a new handle (the autotuner and set_work_plan change it).  Dense crosstalk
 // stages a link's matrix per workgroup, so large ones pay: 1024-taxel hand, 20480 envs x 16 steps
-// 14.5 ms at 512 (now 13.65), 15.3 at 256, 17.3 at 128.  Without it a workgroup shares nothing but its barriers:
-// with noise 128 (200-taxel hand, 1024 envs x 100 steps 0.98 ms, 1.04 at 256, 1.02 at 512; one step
-// of 4096 envs 51.6 us, 51.9, 54.6), and 256 for the shorter clean readout, whose workgroups
-// otherwise spend their time starting (2000 envs x 16 steps 188 us, 192 at 128, 199 at 512).
-int default_target(const tg_readout* h) { return h->xt == 2 ? 512 : (h->noise ? 128 : 256); }
+// 14.5 ms at 512 (now 13.5), 15.3 at 256, 17.3 at 128.  Without it a workgroup shares nothing but its
+// barriers: 256 for the clean readout, whose smaller workgroups spend their time starting (200-taxel
+// hand, 2000 envs x 16 steps 188 us, 192 at 128, 199 at 512), and with noise by the longest link, 4096
+// envs x 16 steps at 512 / 256 / 128 in us:
+//   40 taxels and less: the 200-taxel hand 648 / 620 / 628, but 1024 envs x 100 steps 1020 / 1040 / 980;
+//   to 256, of which 128 lanes hold one or two envs and stand idle past them: 16 links of 48 1816 / 1791 /
+//     2023, 10 of 100 2749 / 2732 / 3047, the 1024-taxel hand 2593 / 2597 / 2813;
+//   longer, where the launch has 512 threads a workgroup anyway: 500, 300, 200 and 24 2582 / 2980 / -,
+//     500 beside twenty of 8 1626 / 1757 / 2172, three of 500 3254 / 3237 / 3256.
+int default_target(const tg_readout* h) {
+  if (h->xt == 2) return 512;
+  if (!h->noise) return 256;
+  int longest = 0;
+  for (int l = 0; l < h->L; ++l)
+    longest = std::max(longest, h->cfg.link_taxel_offset[l + 1] - h->cfg.link_taxel_offset[l]);
+  return longest <= 40 ? 128 : (longest <= 256 ? 256 : 512);
+}
 // Work plan: envs per block for each link (about `target` readouts per block), the
 // (link, first env) items sorted by env, the LDS carve-up sized for the largest link.
 tg_status plan_links(tg_readout* h, int target) {

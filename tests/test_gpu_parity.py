@@ -523,3 +523,22 @@ def test_plans_agree(torch_cuda, counts, E, noise):
 def test_plans_agree_on_more_hands(torch_cuda, counts, E, noise):
     """As test_plans_agree."""
     test_plans_agree(torch_cuda, counts, E, noise)
+
+
+@pytest.mark.parametrize("counts, noise, target", [
+    (synth.C2_LINKS, "banded", 128), ([40, 41], "banded", 256), (synth.C3_LINKS, "banded", 256),
+    ([256, 8], "banded", 256), ([257, 8], "banded", 512), ([500, 8], "off", 256), (synth.C2_LINKS, "dense", 512),
+])
+def test_default_plan(torch_cuda, counts, noise, target):
+    """The default plan's rule, on both sides of its lines."""
+    from paper_2606_22332_amd import binding as B
+    sc = synth.make_scene("c2", num_envs=4, num_steps=1)
+    sc.layout = synth.make_layout(counts)
+    if noise == "off":
+        sc.noise = synth.NoiseParams(seed=sc.noise.seed)
+    elif noise == "dense":
+        sc.noise.xtalk_kind, sc.noise.xtalk_chi, sc.noise.xtalk_sigma = 2, 0.1, 2e-3
+    ro = B.Readout(sc)
+    shape = ro.launch_shape()
+    ro.close()
+    assert shape[0] == target
