@@ -171,3 +171,69 @@ def test_create_destroy_loop_does_not_leak(torch_cuda):
         free.append(torch.cuda.mem_get_info()[0])
     print(dict(free_mb=[round(f / 2**20, 1) for f in free[::8]]))
     assert free[-1] >= free[0] - (2 << 20), (free[0], free[-1])
+
+
+def test_two_handles_replay_graphs_on_two_streams(torch_cuda):
+    """As test_two_handles_on_two_streams, in graph mode: each handle replays its own graph."""
+    torch = torch_cuda
+    from paper_2606_22332_amd import binding as B
+    scenes = [synth.make_scene("c2", num_envs=64, num_steps=5), synth.make_scene("c3", num_envs=24, num_steps=5)]
+    ds = [B.to_device(synth.make_inputs(sc)) for sc in scenes]
+    ros = [B.Readout(sc) for sc in scenes]
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    ref = []
+    for ro, d in zip(ros, ds):
+        ro.alloc_outputs(5)
+        ro.rollout(d, 5)
+        torch.cuda.synchronize()
+        ref.append(snapshot(ro.out))
+        ro.set_graph(True)
+    for _ in range(3):                 # recorded, then replayed
+        for ro, d, st in zip(ros, ds, streams):
+            ro.reset(None, 0, stream=st)
+            ro.rollout(d, 5, stream=st)
+        torch.cuda.synchronize()
+        junk = torch.randn(4096, device="cuda").sum().item()   # eager work between replays
+        assert np.isfinite(junk)
+        for ro, r in zip(ros, ref):
+            assert_same(r, ro.out)
+    for ro in ros:
+        ro.close()
+
+
+@pytest.mark.parametrize("cfg", ["thermal", "spectral", "neural", "dense"])
+def test_graph_replays_follow_the_plan(torch_cuda, cfg):
+    """Graph mode against plain launches for the rollouts of several kernels, each called at two step
+    counters with different inputs, before and after a change of the work plan."""
+    torch = torch_cuda
+    from paper_2606_22332_amd import binding as B
+    E, S = 24, 4
+    sc = synth.make_scene({"neural": "c2", "dense": "c3"}.get(cfg, "c5"), num_envs=E, num_steps=S)
+    kw = {}
+    mask = B.OUT_ALL
+    if cfg == "spectral":
+        sc.thermal.solver, sc.thermal.h_conv, sc.thermal.lag_tau = 1, 10.0, 0.02
+    if cfg == "neural":
+        sc.noise = synth.NoiseParams(seed=sc.noise.seed)
+        mask &= ~B.TG_OUT_NOISY
+        kw = dict(nsdf_params=torch.from_numpy(synth.nsdf_init(len(sc.grids), 5)).cuda(), nsdf_band=1e-3)
+    d = B.to_device(synth.make_inputs(sc))
+    res = {}
+    for graph in (False, True):
+        ro = B.Readout(sc, mask, **kw)
+        ro.set_graph(graph)
+        ro.alloc_outputs(2)
+        res[graph] = []
+        for call, plan in enumerate((None, None, None, 192, None, 512)):
+            if plan:
+                ro.set_work_plan(plan)
+            d.step0 = 2 * call
+            ro.rollout(d, 2, s_in=2 * (call % 2))
+            torch.cuda.synchronize()
+            junk = torch.randn(1000, device="cuda").sum().item()   # eager work between replays
+            assert np.isfinite(junk)
+            res[graph].append(snapshot(ro.out))
+        ro.out = {}
+        ro.close()
+    for a, b in zip(res[False], res[True]):
+        assert_same(a, b)
