@@ -200,23 +200,37 @@ constexpr int MAX_ENVS = 64;
 // steps at 64 / 36 envs: the 200-taxel hand 926 / 701 us, with moving objects 1078 / 804, one step 87 /
 // 66; one link of 512 taxels beside three of 40, 8 and 8, 2048 envs: 2187 / 1361.
 constexpr int MAX_ENVS_DENSE = 36;
+// Share of the launched waves' lanes that belong to a readout, over all links, at a plan's target.
+double lane_fill(const tg_readout* h, int target) {
+  double used = 0, lanes = 0;
+  for (int l = 0; l < h->L; ++l) {
+    const int np = (h->cfg.link_taxel_offset[l + 1] - h->cfg.link_taxel_offset[l] + 7) & ~7;
+    if (np == 0) continue;
+    const int envs = std::max(1, std::min(MAX_ENVS, target / np));
+    used += np;
+    lanes += (double)((envs * np + 63) / 64 * 64) / envs;
+  }
+  return lanes > 0 ? used / lanes : 1.0;
+}
 // Readouts per workgroup of a new handle (the autotuner and set_work_plan change it).  Dense crosstalk
 // stages a link's matrix per workgroup, so large ones pay: 1024-taxel hand, 20480 envs x 16 steps
 // 14.5 ms at 512 (now 13.5), 15.3 at 256, 17.3 at 128.  Without it a workgroup shares nothing but its
-// barriers: 256 for the clean readout, whose smaller workgroups spend their time starting (200-taxel
-// hand, 2000 envs x 16 steps 188 us, 192 at 128, 199 at 512), and with noise by the longest link, 4096
-// envs x 16 steps at 512 / 256 / 128 in us:
-//   40 taxels and less: the 200-taxel hand 648 / 620 / 628, but 1024 envs x 100 steps 1020 / 1040 / 980;
+// barriers.  The clean readout takes 256, as smaller workgroups spend their time starting (200-taxel
+// hand, 2000 envs x 16 steps 188 us, 192 at 128, 199 at 512; 1024-taxel hand, one step of 4096 envs 106
+// us, 118 at 512), but 512 where 256 leaves over 15% of the lanes idle and 512 does not (4096
+// envs x 16 steps, links of 72 taxels 1460 / 1412 us, of 100 1840 / 1725, of 130 1498 / 1345, of 200
+// 1640 / 1505; one step of 4096 envs, links of 100, 110 / 122).  With noise the longest link tells, 4096 envs x 16 steps at 512 / 256 / 128 in us:
+//   40 taxels and less: the 200-taxel hand 648 / 617 / 627, but 1024 envs x 100 steps 1063 / 1020 / 982;
 //   to 256, of which 128 lanes hold one or two envs and stand idle past them: 16 links of 48 1816 / 1791 /
-//     2023, 10 of 100 2749 / 2732 / 3047, the 1024-taxel hand 2593 / 2597 / 2813;
+//     2033, 10 of 100 2749 / 2732 / 3047, the 1024-taxel hand 2593 / 2597 / 2813;
 //   longer, where the launch has 512 threads a workgroup anyway: 500, 300, 200 and 24 2582 / 2980 / -,
 //     500 beside twenty of 8 1626 / 1757 / 2172, three of 500 3254 / 3237 / 3256.
 int default_target(const tg_readout* h) {
   if (h->xt == 2) return 512;
-  if (!h->noise) return 256;
   int longest = 0;
   for (int l = 0; l < h->L; ++l)
     longest = std::max(longest, h->cfg.link_taxel_offset[l + 1] - h->cfg.link_taxel_offset[l]);
+  if (!h->noise) return longest <= 256 && lane_fill(h, 256) < 0.85 && lane_fill(h, 512) >= 0.85 ? 512 : 256;
   return longest <= 40 ? 128 : (longest <= 256 ? 256 : 512);
 }
 // Work plan: envs per block for each link (about `target` readouts per block), the
