@@ -16,7 +16,9 @@
  *
  * The library sorts each cloud into compact chunks of 8 points with bounding spheres in the object
  * frame; a query evaluates every point of the chunks its sphere may reach (a point outside the
- * sphere adds exactly 0).  The sums above are formed from two moments accumulated over those points,
+ * sphere adds exactly 0).  Where few points are in reach of a taxel it keeps a cell grid instead
+ * (cell edge = half the largest sensing radius plus radius_rho) and walks the rows of cells that the
+ * sphere reaches.  The sums above are formed from two moments accumulated over those points,
  * sum P_ij and sum P_ij (p_i - q_j), which give every term of f and tau (the velocity of a point
  * is affine in its position).
  *
@@ -35,7 +37,7 @@
 extern "C" {
 #endif
 
-typedef struct tg_prox tg_prox; /* opaque: sorted clouds and their bounding spheres on the device */
+typedef struct tg_prox tg_prox; /* opaque: sorted clouds and their spheres or cell grids on the device */
 
 typedef struct {
   int32_t num_points;   /* >= 0 */

@@ -7,12 +7,13 @@
 //   sum P v_p  = S0 (v_O + w_O x (q_j - p_O)) + w_O x S1,      S0 = sum P,  S1 = sum P (p_i - q_j)
 //   f   = k rho S0 a + k_s rho [V - a (V . a)],  V = sum P v_p - S0 v_tax
 //   tau = k rho S1 x a
-// The neighbour search runs in the object frame (distances are rotation invariant).  Create sorts
-// each cloud by recursive median splits into chunks of 8 points, and keeps a bounding sphere per
-// chunk, per 8 chunks and per 512 chunks.  Create also splits every link's taxels into tiles of at
-// most 16 neighbouring probes.  A wave takes one tile of one env: its lanes test the spheres
-// against the tile's box grown by the probes' radius, list the chunks that pass, and run through
-// the list eight chunks at a time.  Every (point, probe) pair of a listed chunk is evaluated,
+// The neighbour search runs in the object frame (distances are rotation invariant).  Where few points
+// are in reach of a taxel, a thread takes a probe (tg_prox_cells_kernel; cells_are_faster draws the line).
+// Otherwise create sorts each cloud by recursive median splits into chunks of 8 points, and keeps a
+// bounding sphere per chunk, per 8 chunks and per 512 chunks.  Create also splits every link's taxels
+// into tiles of at most 16 neighbouring probes.  A wave takes one tile of one env: its lanes test the
+// spheres against the tile's box grown by the probes' radius, list the chunks that pass, and run
+// through the list eight chunks at a time.  Every (point, probe) pair of a listed chunk is evaluated,
 // without branches, as two contractions on the matrix cores in FP32 (v_mfma_f32_4x4x1: 16
 // independent 4 x 4 blocks, the points broadcast to the blocks of the tile's probe quads):
 //   p - q = p 1 + (-q), one axis at a time, and
@@ -26,8 +27,8 @@
 // Bound: vector issue: per 256 pairs 12 instructions for the squares, 4 square roots, 4 subtractions
 // and the 7 MFMA, and about as much again of loads, sphere tests and set-up per tile.  Measured on the
 // hand, 4096 envs x 200 taxels x 16 steps, 5000-point clouds: 4.7 ms (4.1 with the expanded square)
-// against 21.4 ms for a thread per probe walking the rows of a cell grid, where the lanes of a wave ran
-// the union of their runs and a pair cost about 13 vector instructions.  About 766 pairs are evaluated
+// against 21.4 ms for a thread a probe, where the lanes of a wave run the union of their rows of cells
+// and a pair costs about 13 vector instructions.  About 766 pairs are evaluated
 // per probe (372 lie inside the sphere).  Before the differences: chunks of 4 points and of 16 evaluate
 // 704 and 856, but cost or save sphere tests: 4.5 ms with 4; a sphere instead of a box around the tile
 // evaluates 986.
@@ -76,6 +77,15 @@ struct ProxSpan {        // taxels [j0, j0 + n) and tiles [t0, t0 + nt) of a wor
   int32_t j0, n, t0, nt;
 };
 
+struct CloudCells {      // one object's cell grid, where the taxels walk cells
+  float origin[3];       // corner of cell (0, 0, 0), object frame
+  float hinv;            // 1 / cell edge
+  int32_t dims[3];       // cells per axis
+  int32_t cell_off;      // first entry of this object's cell table (dims product + 1 entries)
+  float h;               // cell edge
+  int32_t pad[3];
+};
+
 struct ProxParams {
   int32_t E, L, T, n_obj;
   int32_t n_spans, envs;    // envs: envs per workgroup (1 with more than one span)
@@ -84,7 +94,7 @@ struct ProxParams {
   uint32_t key0, key1;
   const float4* tax_a;      // [T] (x_j, R_j)
   const float4* tax_b;      // [T] (n_j, link id as float bits)
-  const CloudDesc* clouds;  // [n_obj]
+  const CloudDesc* clouds;  // [n_obj]  (with cells: n_points alone)
   const ProxSpan* spans;
   const ProxTile* tiles;
   const float4* sphere;     // [chunks] centre, radius (object frame)
@@ -92,6 +102,8 @@ struct ProxParams {
   const float4* super;      // spheres over 64 groups
   const float4* pts;        // [chunks][8] points (x, y, z, 0), object frame
   const float4* mom;        // [chunks][2][4]: x, y, z of four of the chunk's points, then ones
+  const CloudCells* grids;  // [n_obj], null: tiles
+  const int32_t* cells;     // concatenated cell start tables (point index into pts, sorted by cell)
 };
 
 struct ProxLaunch {
@@ -171,14 +183,81 @@ __device__ __forceinline__ int lane_rank(uint64_t mask) {
   return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
 }
 
-// A pose's position and quaternion / all 13 scalars at one column of step s.
+// A pose's position and quaternion at one column of step s.
 __device__ __forceinline__ void load_pose7(const float* state, int64_t cols, int64_t s, int64_t col, float* v) {
 #pragma unroll
   for (int c = 0; c < 7; ++c) v[c] = state[(s * 13 + c) * cols + col];
 }
-__device__ __forceinline__ void load_pose13(const float* state, int64_t cols, int64_t s, int64_t col, float* v) {
+// A taxel's link and its env's object at one step.
+struct ProxFrame {
+  float pL[3], RL[9];   // the link's pose
+  float x[3];           // R_L x_j = q_j - p_L
+  float pO[3], RO[9];   // the object's pose (the origin without object states)
+};
+__device__ __forceinline__ void load_frame(const ProxParams& p, const ProxLaunch& q, int s, int e, const float4& ta,
+                                           int l, bool object, ProxFrame& f) {
+  float v[7], o[7] = {0.f, 0.f, 0.f, 1.f, 0.f, 0.f, 0.f};
+  load_pose7(q.link_state, (int64_t)p.E * p.L, s, (int64_t)e * p.L + l, v);
+  if (object && q.obj_state) load_pose7(q.obj_state, p.E, s, e, o);
+  quat_to_R(v[3], v[4], v[5], v[6], f.RL);
+  quat_to_R(o[3], o[4], o[5], o[6], f.RO);
+  mat_vec(f.RL, ta.x, ta.y, ta.z, f.x);
 #pragma unroll
-  for (int c = 0; c < 13; ++c) v[c] = state[(s * 13 + c) * cols + col];
+  for (int i = 0; i < 3; ++i) {
+    f.pL[i] = v[i];
+    f.pO[i] = o[i];
+  }
+}
+// The six velocities at one column of step s.
+__device__ __forceinline__ void load_velocity(const float* state, int64_t cols, int64_t s, int64_t col, float* v) {
+#pragma unroll
+  for (int c = 0; c < 6; ++c) v[c] = state[(s * 13 + 7 + c) * cols + col];
+}
+// One taxel's channels of step s from its moments (object frame).  npts: its env's points, 0 without
+// an object.
+__device__ __forceinline__ void put_channels(const ProxParams& p, const ProxLaunch& q, int s, int e, int j,
+                                             const float4& tb, const ProxFrame& w, int npts, float S0, float S1x,
+                                             float S1y, float S1z) {
+  const int64_t ET = (int64_t)p.E * p.T, idx = (int64_t)e * p.T + j;
+  const float g = q.gain ? q.gain[idx] : 1.0f;
+  float f[3] = {0.f, 0.f, 0.f}, tau[3] = {0.f, 0.f, 0.f};
+  if (npts > 0) {
+    const float rho = p.density / (float)npts;
+    float a[3], Sw[3], vL[6], vO[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    load_velocity(q.link_state, (int64_t)p.E * p.L, s, (int64_t)e * p.L + __float_as_int(tb.w), vL);
+    if (q.obj_state) load_velocity(q.obj_state, p.E, s, e, vO);
+    mat_vec(w.RL, tb.x, tb.y, tb.z, a);          // a_j
+    mat_vec(w.RO, S1x, S1y, S1z, Sw);            // world-frame sum P (p_i - q_j)
+    // relative velocity moment V = S0 (v_O + w_O x (q - p_O) - v_tax) + w_O x Sw
+    float rq[3], c1[3], c2[3], c3[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) rq[i] = (w.pL[i] + w.x[i]) - w.pO[i];
+    cross3(vO + 3, rq, c1);                      // w_O x (q - p_O)
+    cross3(vL + 3, w.x, c2);                     // w_L x (q - p_L)
+    cross3(vO + 3, Sw, c3);
+    float V[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) V[i] = fmaf(S0, (vO[i] + c1[i]) - (vL[i] + c2[i]), c3[i]);
+    const float vn = fmaf(V[2], a[2], fmaf(V[1], a[1], V[0] * a[0]));
+    const float kr = p.k * rho, ksr = p.k_s * rho;
+    float t3[3];
+    cross3(Sw, a, t3);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      f[i] = fmaf(kr * S0, a[i], ksr * fmaf(-a[i], vn, V[i]));
+      tau[i] = kr * t3[i];
+    }
+  }
+  float fl[3], tl[3];
+  mat_T_vec(w.RL, f[0], f[1], f[2], fl);
+  mat_T_vec(w.RL, tau[0], tau[1], tau[2], tl);
+  float* out = q.ft + (int64_t)s * 6 * ET + idx;
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    __builtin_nontemporal_store(g * fl[i], out + i * ET);
+    __builtin_nontemporal_store(g * tl[i], out + (3 + i) * ET);
+  }
+  if (q.mass) __builtin_nontemporal_store(S0, q.mass + (int64_t)s * ET + idx);
 }
 }  // namespace
 
@@ -191,7 +270,7 @@ __global__ __launch_bounds__(PX_THREADS, 4) void tg_prox_kernel(const ProxParams
   __shared__ int32_t s_groups[PX_WAVES][64];
   __shared__ int32_t s_oid[PX_ENVS];
   __shared__ int32_t s_next;
-  const int64_t ET = (int64_t)p.E * p.T, EL = (int64_t)p.E * p.L;
+  const int64_t EL = (int64_t)p.E * p.L;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int e_blk = blockIdx.x / p.n_spans;
   const ProxSpan sp = p.spans[blockIdx.x - e_blk * p.n_spans];
@@ -311,7 +390,7 @@ __global__ __launch_bounds__(PX_THREADS, 4) void tg_prox_kernel(const ProxParams
           else run(n, std::integral_constant<int, 0>{});
           __builtin_amdgcn_wave_barrier();
         };
-        // From 4096 points on a sphere over 64 groups is tested first.
+        // Above 8192 points (128 groups) a sphere over 64 groups is tested first.
         const int n_groups = far > 0.f ? (cd.n_chunks + 7) >> 3 : 0;
         for (int g0 = 0; g0 < n_groups; g0 += 64) {
           if (n_groups > 128 && __builtin_amdgcn_readfirstlane(!near(p.super[cd.super0 + (g0 >> 6)]))) continue;
@@ -363,70 +442,91 @@ __global__ __launch_bounds__(PX_THREADS, 4) void tg_prox_kernel(const ProxParams
     __syncthreads();
     // 3. the channels from the moments, one taxel per thread
     if (tid < ne * sp.n) {
-      const int el = tid / sp.n, j = sp.j0 + tid - el * sp.n, e = e0 + el;
-      const int64_t idx = (int64_t)e * p.T + j;
-      const float4 ta = p.tax_a[j], tb = p.tax_b[j];
-      const int l = __float_as_int(tb.w);
-      const float g = q.gain ? q.gain[idx] : 1.0f;
-      float v[13], RL[9], x[3], a[3], qv[3];
-      load_pose13(q.link_state, EL, s, (int64_t)e * p.L + l, v);
-      quat_to_R(v[3], v[4], v[5], v[6], RL);
-      mat_vec(RL, ta.x, ta.y, ta.z, x);            // R_L x_j (q_j - p_L)
-      mat_vec(RL, tb.x, tb.y, tb.z, a);            // a_j
-#pragma unroll
-      for (int i = 0; i < 3; ++i) qv[i] = v[i] + x[i];
-      const int oid = s_oid[el];
-      const float4 sum = s_sum[tid];
-      const float S0 = sum.x, S1[3] = {sum.y, sum.z, sum.w};
-      float RO[9] = {1.f, 0.f, 0.f, 0.f, 1.f, 0.f, 0.f, 0.f, 1.f}, pO[3] = {0.f, 0.f, 0.f};
-      float vO[3] = {0.f, 0.f, 0.f}, wO[3] = {0.f, 0.f, 0.f};
-      const int npts = oid >= 0 ? p.clouds[oid].n_points : 0;
-      if (oid >= 0 && q.obj_state) {
-        float o[13];
-        load_pose13(q.obj_state, p.E, s, e, o);
-        quat_to_R(o[3], o[4], o[5], o[6], RO);
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-          pO[i] = o[i];
-          vO[i] = o[7 + i];
-          wO[i] = o[10 + i];
-        }
-      }
-      float f[3] = {0.f, 0.f, 0.f}, tau[3] = {0.f, 0.f, 0.f};
-      if (npts > 0) {
-        const float rho = p.density / (float)npts;
-        float Sw[3];
-        mat_vec(RO, S1[0], S1[1], S1[2], Sw);      // world-frame sum P (p_i - q_j)
-        // relative velocity moment V = S0 (v_O + w_O x (q - p_O) - v_tax) + w_O x Sw
-        float rq[3] = {qv[0] - pO[0], qv[1] - pO[1], qv[2] - pO[2]}, c1[3], c2[3], c3[3];
-        cross3(wO, rq, c1);                        // w_O x (q - p_O)
-        cross3(v + 10, x, c2);                     // w_L x (q - p_L)
-        cross3(wO, Sw, c3);
-        float V[3];
-#pragma unroll
-        for (int i = 0; i < 3; ++i) V[i] = fmaf(S0, (vO[i] + c1[i]) - (v[7 + i] + c2[i]), c3[i]);
-        const float vn = fmaf(V[2], a[2], fmaf(V[1], a[1], V[0] * a[0]));
-        const float kr = p.k * rho, ksr = p.k_s * rho;
-        float t3[3];
-        cross3(Sw, a, t3);
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-          f[i] = fmaf(kr * S0, a[i], ksr * fmaf(-a[i], vn, V[i]));
-          tau[i] = kr * t3[i];
-        }
-      }
-      float fl[3], tl[3];
-      mat_T_vec(RL, f[0], f[1], f[2], fl);
-      mat_T_vec(RL, tau[0], tau[1], tau[2], tl);
-      float* out = q.ft + (int64_t)s * 6 * ET + idx;
-#pragma unroll
-      for (int i = 0; i < 3; ++i) {
-        __builtin_nontemporal_store(g * fl[i], out + i * ET);
-        __builtin_nontemporal_store(g * tl[i], out + (3 + i) * ET);
-      }
-      if (q.mass) __builtin_nontemporal_store(S0, q.mass + (int64_t)s * ET + idx);
+      const int el = tid / sp.n, j = sp.j0 + tid - el * sp.n, e = e0 + el, oid = s_oid[el];
+      const float4 tb = p.tax_b[j], sum = s_sum[tid];
+      ProxFrame w;
+      load_frame(p, q, s, e, p.tax_a[j], __float_as_int(tb.w), oid >= 0, w);
+      put_channels(p, q, s, e, j, tb, w, oid >= 0 ? p.clouds[oid].n_points : 0, sum.x, sum.y, sum.z, sum.w);
     }
     __syncthreads();   // the shared arrays belong to the next step
+  }
+}
+
+// Few points in reach of a taxel: a thread a probe.  Each cloud lies in a uniform cell grid, cell edge
+// half the largest sensing radius, points sorted by cell, x fastest.  A probe visits the rows of cells
+// (fixed y and z) that its sphere reaches; in each the sphere's chord fixes the cells, one contiguous
+// run of points.  Neighbouring lanes hold neighbouring taxels of one link and walk nearly the same
+// cells; the steps are independent, a block row each.  6 waves a SIMD (80 registers, 8 spilled) against
+// 5 without spills: 4096 envs x 200 taxels x 16 steps, 5000 points, R = 1 mm 1.29 ms, 1.36; 3 mm 2.74, 3.00.
+__global__ __launch_bounds__(PX_THREADS, 6) void tg_prox_cells_kernel(const ProxParams p, const ProxLaunch q) {
+  const int64_t idx = (int64_t)blockIdx.x * PX_THREADS + threadIdx.x;
+  if (idx >= (int64_t)p.E * p.T) return;
+  const int e = (int)(idx / p.T), j = (int)(idx - (int64_t)e * p.T);
+  const float4 ta = p.tax_a[j], tb = p.tax_b[j];
+  for (int s = blockIdx.y; s < q.n_steps; s += gridDim.y) {
+    int oid = q.obj_id[(int64_t)s * p.E + e];
+    oid = oid >= 0 && oid < p.n_obj ? oid : -1;
+    ProxFrame w;
+    load_frame(p, q, s, e, ta, __float_as_int(tb.w), oid >= 0, w);
+    float S0 = 0.f, S1[3] = {0.f, 0.f, 0.f};
+    if (oid >= 0) {
+      float qo[3], R = ta.w;
+      mat_T_vec(w.RO, (w.pL[0] + w.x[0]) - w.pO[0], (w.pL[1] + w.x[1]) - w.pO[1], (w.pL[2] + w.x[2]) - w.pO[2], qo);
+      if (p.radius_rho > 0.f) {
+        uint32_t x0 = (uint32_t)e, x1 = (uint32_t)j, x2 = (uint32_t)(q.step0 + s), x3 = 9u;
+        philox4x32_10(x0, x1, x2, x3, p.key0, p.key1);
+        R = R + fmaf(u01(x0), p.two_rho, p.neg_rho);
+        R = R > 0.f ? R : 0.f;
+      }
+      const CloudCells cd = p.grids[oid];
+      const float R2 = R * R;
+      // the culling uses a radius grown by a relative 1e-5 (and 0.1 um), so rounding never drops a row
+      // or cell that holds a point inside the sphere; the point test is exact
+      const float Rc = fmaf(R, 1.00001f, 1e-7f), Rc2 = Rc * Rc;
+      int lo[3], hi[3];
+      bool empty = !(R > 0.f);
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        const float u0 = (qo[i] - Rc - cd.origin[i]) * cd.hinv, u1 = (qo[i] + Rc - cd.origin[i]) * cd.hinv;
+        // NaN or entirely outside the grid: no points in range
+        if (!(u1 >= 0.f) || !(u0 < (float)cd.dims[i])) empty = true;
+        lo[i] = u0 > 0.f ? (int)u0 : 0;
+        hi[i] = u1 < (float)(cd.dims[i] - 1) ? (int)u1 : cd.dims[i] - 1;
+      }
+      if (!empty) {
+        const int32_t* cs = p.cells + cd.cell_off;
+        for (int cz = lo[2]; cz <= hi[2]; ++cz) {
+          const float zl = fmaf((float)cz, cd.h, cd.origin[2]);
+          const float ez = fmaxf(fmaxf(zl - qo[2], qo[2] - (zl + cd.h)), 0.f);
+          for (int cy = lo[1]; cy <= hi[1]; ++cy) {
+            const float yl = fmaf((float)cy, cd.h, cd.origin[1]);
+            const float ey = fmaxf(fmaxf(yl - qo[1], qo[1] - (yl + cd.h)), 0.f);
+            const float c2 = Rc2 - fmaf(ey, ey, ez * ez);
+            if (!(c2 > 0.f)) continue;
+            const float half = __builtin_amdgcn_sqrtf(c2);
+            const float x0 = (qo[0] - half - cd.origin[0]) * cd.hinv, x1 = (qo[0] + half - cd.origin[0]) * cd.hinv;
+            const int ax = x0 > (float)lo[0] ? (int)x0 : lo[0];
+            const int bx = x1 < (float)hi[0] ? (int)x1 : hi[0];
+            if (ax > bx) continue;
+            const int row = (cz * cd.dims[1] + cy) * cd.dims[0];
+            const int b = cs[row + ax], t = cs[row + bx + 1];
+            for (int i = b; i < t; ++i) {
+              const float4 pt = p.pts[i];
+              const float dx = pt.x - qo[0], dy = pt.y - qo[1], dz = pt.z - qo[2];
+              const float d2 = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
+              if (d2 < R2) {
+                const float P = R - __builtin_amdgcn_sqrtf(d2);
+                S0 += P;
+                S1[0] = fmaf(P, dx, S1[0]);
+                S1[1] = fmaf(P, dy, S1[1]);
+                S1[2] = fmaf(P, dz, S1[2]);
+              }
+            }
+          }
+        }
+      }
+    }
+    put_channels(p, q, s, e, j, tb, w, oid >= 0 ? p.clouds[oid].n_points : 0, S0, S1[0], S1[1], S1[2]);
   }
 }
 
@@ -558,6 +658,45 @@ void split_tiles(const float* pos, const float* radius, int32_t* idx, int b, int
   split_tiles(pos, radius, idx, b, b + left, link, j0, out);
   split_tiles(pos, radius, idx, b + left, e, link, j0, out);
 }
+
+// Which kernel a handle takes: a tile costs a wave its set-up and the sphere tests however few points are in
+// reach, and small radii make small tiles.  The two sides are nanoseconds per env and step of a full chip,
+// fitted to 20 runs with n, the points that a sphere of the taxels' root mean square radius holds around a
+// point of the clouds (32 of them are tried).  200-taxel hand, 4096 envs x 16 steps, tiles / cells in ms:
+// 5000-point clouds R = 1 mm 7.39 / 1.29, 2 mm 3.32 / 1.65, 2.5 mm 2.45 / 2.14, 3 mm 2.17 / 2.74, 5 mm
+// 2.24 / 6.28, 10 mm 4.69 / 18.5; 300 points, 3 mm 1.68 / 0.76, 10 mm 1.28 / 1.64.
+bool cells_are_faster(const tg_prox_config& cfg, const std::vector<ProxTile>& tiles) {
+  double r2 = 0;
+  int sensing = 0;
+  for (int j = 0; j < cfg.num_taxels; ++j) {
+    const double r = cfg.sensing_radius[j];
+    if (r > 0 && r < INFINITY) {
+      r2 += r * r;
+      ++sensing;
+    }
+  }
+  if (!sensing) return true;
+  r2 /= sensing;
+  int64_t inside = 0, tried = 0;
+  const int per = std::max(1, 32 / cfg.num_objects);
+  for (int o = 0; o < cfg.num_objects && tried < 32; ++o) {
+    const tg_point_cloud& c = cfg.clouds[o];
+    const int n = std::min(per, c.num_points);
+    for (int t = 0; t < n; ++t, ++tried) {
+      const float* a = c.points + 3 * ((int64_t)c.num_points * t / n);
+      const int64_t step = std::max<int64_t>(1, c.num_points / 2048);
+      for (int64_t i = 0; i < c.num_points; i += step) {
+        const float* x = c.points + 3 * i;
+        const float dx = x[0] - a[0], dy = x[1] - a[1], dz = x[2] - a[2];
+        if (dx * dx + dy * dy + dz * dz < (float)r2) inside += step;
+      }
+    }
+  }
+  const double n = tried ? (double)inside / (double)tried : 0.0;
+  double by_tile = 0;
+  for (const ProxTile& t : tiles) by_tile += t.nq == 0 ? 0.45 + 0.05 * std::sqrt(n) : 0.85 + 0.0055 * n;
+  return cfg.num_taxels * (0.04 + 0.0032 * n) < by_tile;
+}
 }  // namespace
 
 extern "C" {
@@ -615,6 +754,8 @@ tg_status tg_prox_create(const tg_prox_config* cfg, tg_prox** out) {
   // A cloud may span at most 2^24 cells of half the largest radius a query can take (at least 0.1 mm).
   const float h = std::max(0.5f * (rmax + cfg->radius_rho), 1e-4f);
   std::vector<CloudDesc> cds(NO);
+  std::vector<CloudCells> grids(NO);
+  std::vector<int32_t> cells;
   std::vector<float4> sphere, group, super, pts, mom;
   auto pad_chunk = [&] {   // points at infinity, out of every reach; their moments 0 times 0
     for (int i = 0; i < PX_CHUNK; ++i) {
@@ -635,8 +776,43 @@ tg_status tg_prox_create(const tg_prox_config* cfg, tg_prox** out) {
         hi[k] = i ? std::max(hi[k], x) : x;
       }
     int64_t ncell = 1;
-    for (int k = 0; k < 3; ++k) ncell *= std::max(1, (int)std::floor((hi[k] - lo[k]) / h) + 1);
+    CloudCells& g = grids[o];
+    for (int k = 0; k < 3; ++k) {
+      g.origin[k] = lo[k];
+      g.dims[k] = std::max(1, (int)std::floor((hi[k] - lo[k]) / h) + 1);
+      ncell *= g.dims[k];
+    }
     if (ncell > (int64_t(1) << 24)) return pfail(nullptr, TG_ERR_UNSUPPORTED, "cloud cell grid too large");
+    g.hinv = 1.0f / h;
+    g.h = h;
+  }
+  const bool use_cells = cells_are_faster(*cfg, tiles);
+  for (int o = 0; o < NO && use_cells; ++o) {   // counting sort of the points by cell (x fastest)
+    const tg_point_cloud& c = cfg->clouds[o];
+    CloudCells& g = grids[o];
+    cds[o] = CloudDesc{};
+    cds[o].n_points = c.num_points;
+    g.cell_off = (int32_t)cells.size();
+    const int64_t ncell = (int64_t)g.dims[0] * g.dims[1] * g.dims[2];
+    std::vector<int32_t> cid(c.num_points), cnt(ncell + 1, 0);
+    for (int i = 0; i < c.num_points; ++i) {
+      int ci[3];
+      for (int k = 0; k < 3; ++k)
+        ci[k] = std::min(std::max((int)((c.points[3 * (int64_t)i + k] - g.origin[k]) * g.hinv), 0), g.dims[k] - 1);
+      cid[i] = (ci[2] * g.dims[1] + ci[1]) * g.dims[0] + ci[0];
+      ++cnt[cid[i] + 1];
+    }
+    for (int64_t k = 0; k < ncell; ++k) cnt[k + 1] += cnt[k];
+    const int32_t base = (int32_t)pts.size();
+    for (int64_t k = 0; k <= ncell; ++k) cells.push_back(base + cnt[k]);
+    pts.resize(pts.size() + c.num_points);
+    for (int i = 0; i < c.num_points; ++i) {
+      const float* x = c.points + 3 * (int64_t)i;
+      pts[base + cnt[cid[i]]++] = make_float4(x[0], x[1], x[2], 0.f);
+    }
+  }
+  for (int o = 0; o < NO && !use_cells; ++o) {
+    const tg_point_cloud& c = cfg->clouds[o];
     std::vector<CloudPoint> cp(c.num_points);
     if (c.num_points) std::memcpy(cp.data(), c.points, c.num_points * sizeof(CloudPoint));
     split_sort(cp.data(), c.num_points, PX_CHUNK);
@@ -664,7 +840,7 @@ tg_status tg_prox_create(const tg_prox_config* cfg, tg_prox** out) {
     }
   }
   const int32_t dummy = (int32_t)sphere.size();
-  pad_chunk();
+  if (!use_cells) pad_chunk();
   tg_prox* hd = new (std::nothrow) tg_prox();
   if (!hd) return pfail(nullptr, TG_ERR_OUT_OF_MEMORY, "host allocation failed");
   ProxParams& p = hd->p;
@@ -689,6 +865,8 @@ tg_status tg_prox_create(const tg_prox_config* cfg, tg_prox** out) {
   if (e == hipSuccess) e = pupload(hd, &p.super, super);
   if (e == hipSuccess) e = pupload(hd, &p.pts, pts);
   if (e == hipSuccess) e = pupload(hd, &p.mom, mom);
+  if (e == hipSuccess && use_cells) e = pupload(hd, &p.grids, grids);
+  if (e == hipSuccess && use_cells) e = pupload(hd, &p.cells, cells);
   if (e != hipSuccess) {
     tg_prox_destroy(hd);
     return pfail(nullptr, TG_ERR_OUT_OF_MEMORY, std::string("device setup: ") + hipGetErrorString(e));
@@ -719,9 +897,13 @@ tg_status tg_prox_rollout(tg_prox* h, const tg_step_inputs* in, float* ft, float
   q.gain = gain;
   q.step0 = in->step;
   q.n_steps = n_steps;
-  const int64_t blocks = (int64_t)((h->p.E + h->p.envs - 1) / h->p.envs) * h->p.n_spans;
-  hipLaunchKernelGGL(tg_prox_kernel, dim3((unsigned)blocks, (unsigned)std::min(n_steps, 65535)), dim3(PX_THREADS), 0,
-                     (hipStream_t)hip_stream, h->p, q);
+  const int64_t blocks = h->p.grids ? ((int64_t)h->p.E * h->p.T + PX_THREADS - 1) / PX_THREADS
+                                    : (int64_t)((h->p.E + h->p.envs - 1) / h->p.envs) * h->p.n_spans;
+  const dim3 grid((unsigned)blocks, (unsigned)std::min(n_steps, 65535));
+  if (h->p.grids)
+    hipLaunchKernelGGL(tg_prox_cells_kernel, grid, dim3(PX_THREADS), 0, (hipStream_t)hip_stream, h->p, q);
+  else
+    hipLaunchKernelGGL(tg_prox_kernel, grid, dim3(PX_THREADS), 0, (hipStream_t)hip_stream, h->p, q);
   const hipError_t e = hipGetLastError();
   return e == hipSuccess ? TG_OK : pfail(h, TG_ERR_HIP, hipGetErrorString(e));
 }

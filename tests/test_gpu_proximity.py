@@ -325,6 +325,27 @@ def test_one_taxel_without_a_place_leaves_the_others(torch_cuda, taxel, odd):
     assert np.all(g_m[..., taxel] == 0)
 
 
+@pytest.mark.parametrize("radius, points", [(0.001, 5000), (0.002, 5000), (0.0025, 5000), (0.003, 5000), (0.004, 5000),
+                                            (0.01, 30), (0.01, 100), (0.01, 300), (0.02, 1), (0.02, 0)])
+@pytest.mark.parametrize("moving", [False, True])
+def test_few_points_in_reach(torch_cuda, radius, points, moving):
+    """Radii and clouds on both sides of the line between the two kernels (a thread a probe, tiles of
+    probes), with radius noise, gains, envs without an object and an object without points."""
+    sc, inp, _ = scene(13, 3, moving)
+    clouds = synth.surface_clouds(sc.grids, max(points, 1), seed=31)
+    clouds = [c[:points] for c in clouds]
+    clouds[2] = clouds[2][:0]
+    oid = inp.obj_id.copy()
+    oid[:, 4], oid[:, 7], oid[:, 9] = -1, 99, 2
+    inp.obj_id = oid
+    gain = np.random.default_rng(6).uniform(0.8, 1.2, (sc.num_envs, sc.layout.num_taxels)).astype(np.float32)
+    kw = dict(radius=radius, seed=77, radius_rho=0.1 * radius)
+    g_ft, g_m = run_gpu(sc, clouds, inp, gain=gain, **kw)
+    ref = run_oracle(sc, clouds, inp, gain=gain, **kw)
+    check(g_ft, g_m, ref, velocity_scale(inp, sc), radius=1.1 * radius, n_pts=max(points, 1), gain=gain)
+    assert np.all(g_ft[:, :, [4, 7, 9]] == 0) and np.all(g_m[:, [4, 7, 9]] == 0)
+
+
 def run_oracle_radii(sc, clouds, inp, radii, **kw):
     lay = sc.layout
     return oracle.prox_run(lay.link_offset, lay.pos, lay.normal, radii, clouds, inp.link_state, inp.obj_id,
