@@ -667,11 +667,12 @@ void split_tiles(const float* pos, const float* radius, int32_t* idx, int b, int
 // 2.24 / 6.28, 10 mm 4.69 / 18.5; 300 points, 3 mm 1.68 / 0.76, 10 mm 1.28 / 1.64.
 bool cells_are_faster(const tg_prox_config& cfg, const std::vector<ProxTile>& tiles) {
   double r2 = 0;
+  const double rho = cfg.radius_rho;
   int sensing = 0;
   for (int j = 0; j < cfg.num_taxels; ++j) {
     const double r = cfg.sensing_radius[j];
-    if (r > 0 && r < INFINITY) {
-      r2 += r * r;
+    if (r + rho > 0 && r + rho < INFINITY) {
+      r2 += r * r + rho * rho / 3;
       ++sensing;
     }
   }
