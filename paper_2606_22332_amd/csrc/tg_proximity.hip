@@ -776,14 +776,15 @@ tg_status tg_prox_create(const tg_prox_config* cfg, tg_prox** out) {
         lo[k] = i ? std::min(lo[k], x) : x;
         hi[k] = i ? std::max(hi[k], x) : x;
       }
-    int64_t ncell = 1;
+    double ncell = 1;   // (also of clouds whose counts no integer holds)
     CloudCells& g = grids[o];
     for (int k = 0; k < 3; ++k) {
       g.origin[k] = lo[k];
-      g.dims[k] = std::max(1, (int)std::floor((hi[k] - lo[k]) / h) + 1);
-      ncell *= g.dims[k];
+      const double n = std::floor((hi[k] - lo[k]) / h) + 1.0;
+      g.dims[k] = (int)std::min(16777216.0, n);
+      ncell *= n;
     }
-    if (ncell > (int64_t(1) << 24)) return pfail(nullptr, TG_ERR_UNSUPPORTED, "cloud cell grid too large");
+    if (!(ncell <= 16777216.0)) return pfail(nullptr, TG_ERR_UNSUPPORTED, "cloud cell grid too large");
     g.hinv = 1.0f / h;
     g.h = h;
   }

@@ -97,3 +97,17 @@ def test_create_rejects_bad_sizes_on_the_host(field, value, status):
     setattr(cfg, field, value)
     h = C.c_void_p()
     assert lib.tg_readout_create(C.byref(cfg), C.byref(h)) == status and not h.value
+
+
+@pytest.mark.skipif(not os.path.exists(LIB), reason="library not built")
+@pytest.mark.parametrize("side", [0.2, 1.0, (2.0 ** 22 - 0.5) * 0.005, 3e7, 3e38])
+def test_proximity_refuses_clouds_of_too_many_cells(side):
+    """More than 2^24 cells of half the sensing radius, up to counts whose product is a multiple of 2^64
+    and counts that no integer holds."""
+    from types import SimpleNamespace
+    import numpy as np
+    from paper_2606_22332_amd import binding as B, synth
+    sc = SimpleNamespace(layout=synth.make_layout([4]), num_envs=1)
+    cloud = np.array([[0, 0, 0], [1, 1, 1]], np.float64) * side
+    with pytest.raises(B.TgError, match="cell grid too large"):
+        B.Proximity(sc, [cloud.astype(np.float32)], radius=1e-3 if side < 2 else 0.01)
