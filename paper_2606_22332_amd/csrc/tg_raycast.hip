@@ -312,7 +312,9 @@ __global__ __launch_bounds__(64, 6) void tg_ray_kernel(const RayParams p, const 
           x4 = make_float4(qo[0], qo[1], qo[2], ta.w);
           const RayNode rt = p.root[w.oid];
           root = make_int2(__float_as_int(rt.lo.w), __float_as_int(rt.hi.w));
-          in = box_d2(rt, x4) < ta.w * ta.w;
+          // (a centre in the box may need the ray, also where the square of its radius is 0 in FP32)
+          const float d2 = box_d2(rt, x4);
+          in = d2 < ta.w * ta.w || d2 == 0.f;
         }
         if (!in) put(p, q, s, idx, w, 0.f, -1);
       }

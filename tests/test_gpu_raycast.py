@@ -193,3 +193,20 @@ def test_rejects_bad_meshes(torch_cuda):
     bad = v.copy(); bad[2, 1] = np.nan
     with pytest.raises(B.TgError):
         B.Raycast(sc, [(bad, np.array([[0, 1, 2]], np.int32))])
+
+
+def test_radii_whose_squares_vanish(torch_cuda):
+    """Probes of 1e-30 m, whose squared radius is 0 in FP32, beside ordinary ones and probes of 0 (which
+    sense nothing): a centre inside the mesh still has its axial depth."""
+    sc = synth.make_scene("c2", num_envs=24, num_steps=4)
+    inp = synth.make_inputs(sc)
+    lay = sc.layout
+    lay.radius = lay.radius.copy()
+    lay.radius[::3] = 1e-30
+    lay.radius[1::9] = 0.0
+    meshes = synth.object_meshes(sc.grids)
+    g = run_gpu(torch_cuda, sc, inp, meshes)
+    ref = run_oracle(sc, inp, meshes, tri_query=g[2])
+    check(g, ref, sc, inp, meshes)
+    assert (ref[0][:, :, ::3] > 1e-4).mean() > 0.02
+    assert np.all(g[0][:, :, 1::9] == 0) and np.all(g[2][:, :, 1::9] == -1)
