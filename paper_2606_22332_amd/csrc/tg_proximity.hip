@@ -462,12 +462,13 @@ __global__ __launch_bounds__(PX_THREADS, 6) void tg_prox_cells_kernel(const Prox
   const int64_t idx = (int64_t)blockIdx.x * PX_THREADS + threadIdx.x;
   if (idx >= (int64_t)p.E * p.T) return;
   const int e = (int)(idx / p.T), j = (int)(idx - (int64_t)e * p.T);
-  const float4 ta = p.tax_a[j], tb = p.tax_b[j];
+  const float4 ta = p.tax_a[j];
+  const int l = __float_as_int(p.tax_b[j].w);
   for (int s = blockIdx.y; s < q.n_steps; s += gridDim.y) {
     int oid = q.obj_id[(int64_t)s * p.E + e];
     oid = oid >= 0 && oid < p.n_obj ? oid : -1;
     ProxFrame w;
-    load_frame(p, q, s, e, ta, __float_as_int(tb.w), oid >= 0, w);
+    load_frame(p, q, s, e, ta, l, oid >= 0, w);
     float S0 = 0.f, S1[3] = {0.f, 0.f, 0.f};
     if (oid >= 0) {
       float qo[3], R = ta.w;
@@ -526,7 +527,12 @@ __global__ __launch_bounds__(PX_THREADS, 6) void tg_prox_cells_kernel(const Prox
         }
       }
     }
-    put_channels(p, q, s, e, j, tb, w, oid >= 0 ? p.clouds[oid].n_points : 0, S0, S1[0], S1[1], S1[2]);
+    // the poses are read again (from cache) rather than held over the walk
+    int s_ = s, j_ = j;
+    asm volatile("" : "+s"(s_), "+v"(j_));
+    const float4 tb = p.tax_b[j_];
+    load_frame(p, q, s_, e, p.tax_a[j_], __float_as_int(tb.w), oid >= 0, w);
+    put_channels(p, q, s_, e, j_, tb, w, oid >= 0 ? p.clouds[oid].n_points : 0, S0, S1[0], S1[1], S1[2]);
   }
 }
 
