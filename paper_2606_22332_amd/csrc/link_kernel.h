@@ -54,7 +54,8 @@ __device__ __forceinline__ Pose pose_from13(const float* v) {
 // covers whole cache lines they go out as non-temporal stores, so that the output stream does not
 // evict the grid bricks the gathers reuse from L2; where runs are short, several links' workgroups
 // share each line, and plain stores let L2 put the line together before it is written
-// (LinkInfo::stream, chosen by plan_links).
+// (LinkInfo::stream, chosen by plan_links).  Launches of few steps may ask for the former everywhere
+// (KLaunch::stream).
 // A store goes through a uniform base (SGPR pair) and a per-lane 32-bit byte offset: the scalar-base
 // form of the vector store, so no per-lane 64-bit address is formed.  (Outputs are never read by the
 // kernel, so the store needs no ordering against its other memory accesses.)
@@ -362,7 +363,7 @@ __global__ void __launch_bounds__(512, 4) tg_link_kernel(const KLaunch qarg) {
     const bool bit = o.depth > p.eta_on;
     const int wbit = (li.off & 63) + k;   // bit position inside this env's window
     if (act) {
-      with_policy(li.stream, [&](auto nt) {
+      with_policy(li.stream | q.stream, [&](auto nt) {
         constexpr int NT = decltype(nt)::value;
         if (q.depth) store_at<NT>(q.depth + (int64_t)s * ET, off4, o.depth);
         if (q.prox) store_at<NT>(q.prox + (int64_t)s * ET, off4, o.prox);
@@ -552,7 +553,7 @@ __global__ void __launch_bounds__(512, 4) tg_link_kernel(const KLaunch qarg) {
       }
       if (act && q.ft_noisy) {
         float* f = q.ft_noisy + (int64_t)s * 6 * ET;
-        with_policy(li.stream, [&](auto nt) {
+        with_policy(li.stream | q.stream, [&](auto nt) {
 #pragma unroll
           for (int c = 0; c < 6; ++c) store_at<decltype(nt)::value>(f + c * ET, off4, fo[c]);
         });

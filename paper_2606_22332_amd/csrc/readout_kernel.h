@@ -78,6 +78,7 @@ __device__ __forceinline__ void check_object_id(uint32_t* err, int oid, int n_ob
 struct KLaunch {
   const KParams* kc;
   int32_t n_steps;
+  int32_t stream;                // 1: every link's outputs go out with non-temporal stores
   int64_t step0;
   // inputs (per step strides implied by sizes)
   const float* link_state;       // [S][13][E*L]

@@ -186,11 +186,37 @@ KernelFn select_kernel(int noise, int xt, int hy, int obj, int full) {
 // per 100 steps of 1024 envs on the 200-taxel hand); whole ones only take L2's room from the grids.
 // Hands of 12 to 32 equal links, 4096 envs x 16 steps, all stores plain / non-temporal, in us:
 //   runs of whole pieces: links of 16 taxels 751 / 577, 32 1177 / 1059, 48 2231 / 2025, 64 2205 / 1974;
-//   others: 8 909 / 1919, 24 1052 / 1745, 40 1764 / 2144, 56 2477 / 2670, 60 2465 / 2817, 72 2849 / 2751.
+//   others: 8 909 / 1919, 24 1052 / 1745.
+// Where no link is short, few pieces are shared, and a noisy readout, slower per output, streams them.  Medians
+// over 5 to 11 placements of the outputs (which alone move a launch by a tenth), plain / non-temporal: banded
+// noise, links of 40 taxels 1298 / 1227, of 56 1549 / 1458, of 60 1399 / 1287 (with every output 1610 / 1415), of 39 to
+// 63 1102 / 1022, 1192 / 1107 and 1275 / 1204, of 44 1778 / 1682; with dense crosstalk, 8 steps, 60 932 / 844.
+// The clean readout streams runs of whole 32-byte sectors (40 at 8 steps 379 / 329, 56 833 / 686), or of 56
+// taxels and more (60 756 / 694, with every output 1100 / 812), and others not (39 to 63 546 / 603 and 596 / 806, 44
+// 753 / 808, at 32 steps 1519 / 2126).
 // On the 1024-taxel hand (links of 25 to 128 taxels, 20480 envs x 16 steps, dense crosstalk), with the
 // bound at 33 / 48 / 64 / 90 / 100 taxels, 15.20 / 14.87 / 14.73 / 14.79 / 14.98 ms; 15.87 all
 // non-temporal, 16.1 all plain.
-bool stream_stores(int off, int n, int T) { return n >= 64 || (off % 16 == 0 && n % 16 == 0 && T % 16 == 0); }
+bool stream_stores(int off, int n, int T, int shortest, bool noise) {
+  const auto whole = [&](int floats) { return off % floats == 0 && n % floats == 0 && T % floats == 0; };
+  return n >= 64 || shortest >= 56 || whole(16) || (shortest >= 36 && (noise || whole(8)));
+}
+// Whether a launch streams every link's outputs whatever their runs (KLaunch::stream): where the noise state
+// stays in the Infinity Cache (256 MB) from launch to launch if the outputs pass it by, and the launch is
+// short enough that this outweighs what the shared pieces cost each step.  Plain / non-temporal, us a launch
+// with banded noise at 512 readouts a workgroup:
+//   the 1024-taxel hand, 4096 envs (210 MB of state) 1 step 253 / 221, 4 steps 635 / 594, 16 2141 / 2312, with
+//     dense crosstalk 280 / 253, 705 / 653 and 8 steps 1296 / 1260; 2048 envs (105 MB) 4 steps 333 / 335, 8
+//     609 / 626; 20480 envs 1 step 1237 / 1239, 4 3125 / 3375;
+//   20 links of 24, 8192 envs (197 MB) 1 step 262 / 209, 2 388 / 340, 4 649 / 712; 4096 envs (98 MB) 106 / 113;
+//   the 200-taxel hand, 16384 envs (164 MB) 1 step 244 / 220, 4 620 / 887.
+bool stream_launch(const tg_readout* h, int n_steps) {
+  if (!h->noise) return false;
+  const double per = (h->kp.drift_sigma != 0.f ? 24.0 : 0.0) + (h->hy > 0 ? 24.0 : 0.0) + (h->hy == 2 ? 24.0 : 0.0) + 2.0;
+  const double state = per * h->E * h->T;
+  const int most = h->T >= 40 * h->L ? 8 : (h->T >= 24 * h->L ? 2 : 1);   // by the links' mean length
+  return state >= 120e6 && state <= 240e6 && n_steps <= most;
+}
 // Most envs of a workgroup: 8-taxel links then fill 512 lanes.  (36, one prefetched scalar a lane,
 // and idle waves kept: 200-taxel hand, 1021 envs x 33 steps 595 us against 385, one step of 4096
 // envs 62 against 58.)
@@ -239,7 +265,9 @@ tg_status plan_links(tg_readout* h, int target) {
   const int L = h->L, E = h->E;
   const int32_t* off = h->cfg.link_taxel_offset;
   const int max_envs = h->xt == 2 ? MAX_ENVS_DENSE : MAX_ENVS;
-  int nthr = 64;
+  int nthr = 64, shortest = 512;
+  for (int l = 0; l < L; ++l)
+    if (off[l + 1] > off[l]) shortest = std::min(shortest, off[l + 1] - off[l]);
   for (int l = 0; l < L; ++l) {
     LinkInfo& li = h->links[l];
     li.off = off[l];
@@ -250,7 +278,7 @@ tg_status plan_links(tg_readout* h, int target) {
     li.envs = std::max(1, std::min(std::min(E, max_envs), target / li.np));
     li.nwin = li.n > 0 ? ((li.off + li.n - 1) >> 6) - (li.off >> 6) + 1 : 1;
     li.nt = (6 * li.envs + 15) / 16;
-    li.stream = stream_stores(li.off, li.n, h->T);
+    li.stream = stream_stores(li.off, li.n, h->T, shortest, h->noise);
     const int n16 = ((li.n + 15) / 16) * 16, n32 = ((li.n + 31) / 32) * 32;
     li.kp = n32 + 8;    // B staging column stride (bf16): K tiles of 32, 16-byte aligned columns
     li.kpd = n16 + 4;   // result staging row stride (floats)
@@ -953,6 +981,7 @@ static tg_status launch_rollout(tg_readout* h, const tg_step_inputs* in, const t
   KLaunch k{};
   k.kc = h->d_kp;
   k.n_steps = n_steps;
+  k.stream = stream_launch(h, n_steps);
   k.step0 = in->step;
   k.link_state = in->link_state;
   k.obj_state = in->obj_state;

@@ -544,3 +544,31 @@ def test_default_plan(torch_cuda, counts, noise, target):
     shape = ro.launch_shape()
     ro.close()
     assert shape[0] == target
+
+
+@pytest.mark.parametrize("counts, envs, steps", [([40] * 16, 4096, 2), ([24] * 20, 8192, 2), ([24] * 20, 8192, 3),
+                                                  ([66, 61, 35, 47], 8192, 1)])
+def test_streamed_launches(torch_cuda, counts, envs, steps):
+    """Short launches whose noise state fits the Infinity Cache (131, 197 and 82 MB) store every output
+    non-temporally, others by link: the first envs equal those of a handle of 8 envs, bit for bit."""
+    torch = torch_cuda
+    from paper_2606_22332_amd import binding as B
+    sc = synth.make_scene("c2", num_envs=8, num_steps=steps)
+    sc.layout = synth.make_layout(counts)
+    inp = synth.make_inputs(sc)
+    outs = []
+    for E in (8, envs):
+        sc.num_envs = E
+        d = B.to_device(inp)
+        d.link_state = d.link_state.repeat(1, 1, E // 8).contiguous()
+        d.obj_id = d.obj_id.repeat(1, E // 8).contiguous()
+        ro = B.Readout(sc)
+        ro.alloc_outputs(steps)
+        ro.rollout(d, steps)
+        torch.cuda.synchronize()
+        outs.append({k: v.clone() for k, v in ro.out.items()})
+        ro.close()
+    small, large = outs
+    for k in ("depth", "prox", "ft", "ft_noisy", "surfdist", "normal"):
+        env_axis = small[k].dim() - 2
+        assert torch.equal(small[k], large[k].narrow(env_axis, 0, 8)), k
