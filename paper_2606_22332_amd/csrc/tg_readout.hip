@@ -238,6 +238,21 @@ double lane_fill(const tg_readout* h, int target) {
   }
   return lanes > 0 ? used / lanes : 1.0;
 }
+// Share of a CU's lanes that belong to a readout when every workgroup keeps all its waves (with noise), of
+// which the registers allow 16 a CU.
+double cu_fill(const tg_readout* h, int target) {
+  double used = 0, groups = 0;
+  int nw = 1;
+  for (int l = 0; l < h->L; ++l) {
+    const int np = (h->cfg.link_taxel_offset[l + 1] - h->cfg.link_taxel_offset[l] + 7) & ~7;
+    if (np == 0) continue;
+    const int envs = std::max(1, std::min(MAX_ENVS, target / np));
+    nw = std::max(nw, (envs * np + 63) / 64);
+    used += np;
+    groups += 1.0 / envs;
+  }
+  return groups > 0 ? used * (16 / nw) / (1024 * groups) : 1.0;
+}
 // Readouts per workgroup of a new handle (the autotuner and set_work_plan change it).  Dense crosstalk
 // stages a link's matrix per workgroup, so large ones pay: 1024-taxel hand, 20480 envs x 16 steps
 // 14.5 ms at 512 (now 13.5), 15.3 at 256, 17.3 at 128.  Without it a workgroup shares nothing but its
@@ -245,19 +260,22 @@ double lane_fill(const tg_readout* h, int target) {
 // hand, 2000 envs x 16 steps 188 us, 192 at 128, 199 at 512; 1024-taxel hand, one step of 4096 envs 106
 // us, 118 at 512), but 512 where 256 leaves over 15% of the lanes idle and 512 does not (4096
 // envs x 16 steps, links of 72 taxels 1460 / 1412 us, of 100 1840 / 1725, of 130 1498 / 1345, of 200
-// 1640 / 1505; one step of 4096 envs, links of 100, 110 / 122).  With noise the longest link tells, 4096 envs x 16 steps at 512 / 256 / 128 in us:
-//   40 taxels and less: the 200-taxel hand 648 / 617 / 627, but 1024 envs x 100 steps 1063 / 1020 / 982;
-//   to 256, of which 128 lanes hold one or two envs and stand idle past them: 16 links of 48 1816 / 1791 /
-//     2033, 10 of 100 2749 / 2732 / 3047, the 1024-taxel hand 2593 / 2597 / 2813;
-//   longer, where the launch has 512 threads a workgroup anyway: 500, 300, 200 and 24 2582 / 2980 / -,
-//     500 beside twenty of 8 1626 / 1757 / 2172, three of 500 3254 / 3237 / 3256.
+// 1640 / 1505; one step of 4096 envs, links of 100, 110 / 122).  With noise
+// every workgroup keeps the launch's waves; 512 where a CU then holds more readouts than at 256, at 512 / 256 / 128
+// in us with banded noise: the 1024-taxel hand, 4096 envs x 16 steps 2141 / 2212 / 2389, 20480 x 1 1237 / 1327 / 1384; 4 links
+// of 130, 2048 x 16 676 / 705 / 713; 5 of 20, 4096 x 16 267 / 311 / 313; 20 of 24, 1024 x 16 298 / 343 / 341, 8192 x 4 649 / 670 / 701;
+// and above 256 taxels, where the launch has 512 threads a workgroup anyway (500, 300, 200 and 24 2582 / 2980 / -,
+// 500 beside twenty of 8 1626 / 1757 / 2172).  Else 256: links of 40 1428 / 1447 / 1522, 48 1431 / 1357 / 1642,
+// 32 698 / 663 / 682, 16 484 / 473 / 499, 10 of 100, 2048 x 16 1224 / 1127 / 1252, 4 of 200 972 / 870 / 870; but 128 for
+// hands of short links: the 200-taxel one, 1024 x 100 893 / 860 / 845, 4096 x 16 573 / 542 / 545.
 int default_target(const tg_readout* h) {
   if (h->xt == 2) return 512;
   int longest = 0;
   for (int l = 0; l < h->L; ++l)
     longest = std::max(longest, h->cfg.link_taxel_offset[l + 1] - h->cfg.link_taxel_offset[l]);
   if (!h->noise) return longest <= 256 && lane_fill(h, 256) < 0.85 && lane_fill(h, 512) >= 0.85 ? 512 : 256;
-  return longest <= 40 ? 128 : (longest <= 256 ? 256 : 512);
+  if (longest > 256 || cu_fill(h, 512) >= 1.04 * cu_fill(h, 256)) return 512;
+  return longest <= 40 && h->T < 16 * h->L ? 128 : 256;
 }
 // Work plan: envs per block for each link (about `target` readouts per block), the
 // (link, first env) items sorted by env, the LDS carve-up sized for the largest link.

@@ -526,7 +526,8 @@ def test_plans_agree_on_more_hands(torch_cuda, counts, E, noise):
 
 
 @pytest.mark.parametrize("counts, noise, target", [
-    (synth.C2_LINKS, "banded", 128), ([40, 41], "banded", 256), (synth.C3_LINKS, "banded", 256),
+    (synth.C2_LINKS, "banded", 128), ([40, 41], "banded", 256), (synth.C3_LINKS, "banded", 512),
+    ([40] * 16, "banded", 256), ([20] * 5, "banded", 512), ([130] * 4, "banded", 512), ([100] * 10, "banded", 256),
     ([256, 8], "banded", 256), ([257, 8], "banded", 512), ([500, 8], "off", 256), (synth.C2_LINKS, "dense", 512),
     (synth.C2_LINKS, "off", 256), (synth.C3_LINKS, "off", 256), ([20] * 5, "off", 256), ([100] * 3, "off", 512),
     ([130, 72], "off", 512), ([200] * 2, "off", 512), ([300] * 2, "off", 256), ([1], "off", 256),
