@@ -325,6 +325,8 @@ def bench_c4(args) -> dict:
                      "ms_total": train_ms, "ms_per_step": train_ms / args.train_steps,
                      "final_l1_um_median": float(np.median(loss_um)), "final_l1_um_max": float(loss_um.max())},
         "memory_MB": {"grids_fp32": n_obj * sc.grids[0].n ** 3 * 4 / 1e6,
+                      # as the readout stores them: bricks of 3 x 3 x 3 cells with all corners, 256 B each
+                      "grids_bricks": n_obj * -(-(sc.grids[0].n - 1) // 3) ** 3 * 256 / 1e6,
                       "network_bf16": n_obj * 15681 * 2 / 1e6,
                       "network_images": n_obj * 65024 / 1e6},
         "input_gen_s": gen_s,

@@ -3,9 +3,9 @@
 // A block owns one link l for `envs` consecutive environments and runs every step of the
 // launch for them: lane r <-> (env el = r / np, taxel k = r % np), np = n_l rounded up to a
 // multiple of 8, about 128..512 readouts per block whatever the link size (the plan's target), so
-// uneven links waste few lanes; the waves that a short link does not need end at once and leave their
-// slots to other blocks, whose memory latency and arithmetic overlap.  Because a block only ever sees
-// one link, everything that couples taxels stays inside the block:
+// uneven links waste few lanes; in the clean readout the waves that a short link does not need end at
+// once and leave their slots to other blocks, whose memory latency and arithmetic overlap.  Because a
+// block only ever sees one link, everything that couples taxels stays inside the block:
 //   - dense crosstalk C_l Z_l runs on MFMA (16x16x32 BF16) with the six channels of all the
 //     block's envs as the N columns; the link's A fragments are staged in LDS for the launch
 //     (or read from L2 when they do not fit) and Z goes through an LDS staging area;
@@ -218,8 +218,8 @@ __global__ void __launch_bounds__(512, 4) tg_link_kernel(const KLaunch qarg) {
 #define li (*lip)
   const int n = li.n, envs = li.envs;
   const int tid = threadIdx.x;
-  // The threads that work on this link; the waves past them end here (a barrier counts the waves that
-  // are left), so short links do not hold wave slots that the launch's longest link asked for.
+  // The threads that work on this link; waves past them (clean readouts) end here (a barrier counts the
+  // waves that are left), so short links do not hold wave slots that the launch's longest link asked for.
   const int nthr = li.nthr;
   if (tid >= nthr) return;
   LinkLds Ld;   // field by field: the source lives in the constant address space

@@ -456,8 +456,10 @@ __global__ __launch_bounds__(PX_THREADS, 4) void tg_prox_kernel(const ProxParams
 // half the largest sensing radius, points sorted by cell, x fastest.  A probe visits the rows of cells
 // (fixed y and z) that its sphere reaches; in each the sphere's chord fixes the cells, one contiguous
 // run of points.  Neighbouring lanes hold neighbouring taxels of one link and walk nearly the same
-// cells; the steps are independent, a block row each.  6 waves a SIMD (80 registers, 8 spilled) against
-// 5 without spills: 4096 envs x 200 taxels x 16 steps, 5000 points, R = 1 mm 1.29 ms, 1.36; 3 mm 2.74, 3.00.
+// cells; the steps are independent, a block row each.  The poses are
+// read again, from cache, after the walk: 74 registers, 6 waves a SIMD and no scratch.  Held over it, 8
+// spilled: 4096 envs x 200 taxels x 16 steps, 5000 points, R = 1 mm 1.22 ms, 1.29 held; 2 mm 1.52, 1.67; 20
+// points at 10 mm 0.53, 0.57; 8 waves, which spill, 1.20, 1.50 and 0.55.
 __global__ __launch_bounds__(PX_THREADS, 6) void tg_prox_cells_kernel(const ProxParams p, const ProxLaunch q) {
   const int64_t idx = (int64_t)blockIdx.x * PX_THREADS + threadIdx.x;
   if (idx >= (int64_t)p.E * p.T) return;
@@ -670,7 +672,8 @@ void split_tiles(const float* pos, const float* radius, int32_t* idx, int b, int
 // fitted to 20 runs with n, the points that a sphere of the taxels' root mean square radius holds around a
 // point of the clouds (32 of them are tried).  200-taxel hand, 4096 envs x 16 steps, tiles / cells in ms:
 // 5000-point clouds R = 1 mm 7.39 / 1.29, 2 mm 3.32 / 1.65, 2.5 mm 2.45 / 2.14, 3 mm 2.17 / 2.74, 5 mm
-// 2.24 / 6.28, 10 mm 4.69 / 18.5; 300 points, 3 mm 1.68 / 0.76, 10 mm 1.28 / 1.64.
+// 2.24 / 6.28, 10 mm 4.69 / 18.5; 300 points, 3 mm 1.68 / 0.76, 10 mm 1.28 / 1.64 (the cells while the
+// poses were held over the walk, 5 to 9% slower than now).
 bool cells_are_faster(const tg_prox_config& cfg, const std::vector<ProxTile>& tiles) {
   double r2 = 0;
   const double rho = cfg.radius_rho;
